@@ -79,10 +79,14 @@ def upload(strides, dtype):
     return out
 
 
+# Profile slots keep their numbers whatever launches a layer takes.  The next
+# four names describe the recorded traces of builds that ran the wide stride-1
+# layers in two launches (contraction and tap sum) and the others in a narrow
+# and a wide kernel; slot_kernel() names what the library launches now.
 def layer_kernel_name(cin: int, cout: int, stride: int, dtype: str) -> str:
-    """The library's kernel for a layer: the wide-layer kernel takes more than
-    8 input chunks of 16 channels with cout >= 32, or more than 4 with
-    cout >= 128; every other layer the narrow one."""
+    """Kernel of a one-launch layer in such a trace: the wide-layer kernel takes
+    more than 8 input chunks of 16 channels with cout >= 32, or more than 4
+    with cout >= 128; every other layer the narrow one."""
     nch = cin // 16
     wide = (nch > 8 and cout >= 32) or (nch > 4 and cout >= 128)
     return f"layer_kernel{'_wide' if wide else ''}<{cin},{cout},{stride},{dtype}>"
@@ -122,6 +126,15 @@ def kernel_name(slot: int, wl, ups=(), points=False) -> str:
     if layer_split(l, wl):
         return f"tap_sum_kernel<{sp.cout},{wl.dtype}>"
     return layer_kernel_name(sp.cin, sp.cout, sp.stride, wl.dtype)
+
+
+def slot_kernel(slot: int, wl, ups=(), points=False) -> str:
+    """The kernel the library launches for a profile slot: one per layer."""
+    L = len(wl.layers)
+    if 2 <= slot < L + 2:
+        sp = wl.layers[slot - 2]
+        return f"layer_kernel<{sp.cin},{sp.cout},{sp.stride},{wl.dtype}>"
+    return kernel_name(slot, wl, ups, points)
 
 
 def layer_work(wl, l: int, act, pairs, launches: int):
@@ -253,15 +266,13 @@ def cpu_baseline_points(wl, ws, spec, pw, batches, first, budget_s):
 # HBM traffic of the dominant kernel from --pmc FETCH_SIZE / WRITE_SIZE runs
 # scaled by what the same counters read for a plain copy of known size.
 # --------------------------------------------------------------------------
-KERNEL_SOURCES = ("detect.hip", "layer.hip", "contract.hip", "misc.hip", "upsample.hip", "pfn.hip",
+KERNEL_SOURCES = ("detect.hip", "layer.hip", "misc.hip", "upsample.hip", "pfn.hip",
                   "device_common.h", "sscater_internal.h")
 
 
 # the device-code sources each kernel family is built from
 KERNEL_FILES = {
     "layer_kernel": ("layer.hip", "device_common.h", "sscater_internal.h"),
-    "contract_kernel": ("contract.hip", "device_common.h", "sscater_internal.h"),
-    "tap_sum_kernel": ("contract.hip", "device_common.h", "sscater_internal.h"),
     "detect_kernel": ("detect.hip", "device_common.h", "sscater_internal.h"),
     "detect_sorted_kernel": ("detect.hip", "device_common.h", "sscater_internal.h"),
     "upsample_kernel": ("upsample.hip", "device_common.h", "sscater_internal.h"),
@@ -359,7 +370,8 @@ def launches_per_stride(kernel: str, wl) -> int:
     L = len(wl.layers)
     names = [kernel_name(1 + l, wl) for l in range(1, L + 1)]
     names += [kernel_name(L + 1 + l, wl) for l in range(1, L + 1) if layer_split(l, wl)]
-    return sum(1 for n in names if n == kernel)
+    now = [slot_kernel(1 + l, wl) for l in range(1, L + 1)]
+    return sum(1 for n in now if n == kernel) or sum(1 for n in names if n == kernel)
 
 
 def _csv_rows(path):
@@ -415,7 +427,7 @@ def digest_sweep_trace(path: str, steps: int, warmup: int) -> str:
            "|---|---|---|---|---|---|"]
     for ci in S.SWEEP_CIN:
         for co in S.SWEEP_COUT:
-            k = layer_kernel_name(ci, co, 1, "f32")
+            k = f"layer_kernel<{ci},{co},1,f32>"
             v = by.get(k, [])
             if len(v) < 2 * span:
                 continue
@@ -646,7 +658,7 @@ def run_streams(wl, ws, K: int, W: int, n: int, cpu_seconds, no_cpu: bool, batch
         for slot in range(L + 2):
             if cnt[slot] == 0:
                 continue
-            k = kernels.setdefault(kernel_name(slot, wl), {"ms": 0.0, "launches": 0, "flops": 0.0})
+            k = kernels.setdefault(slot_kernel(slot, wl), {"ms": 0.0, "launches": 0, "flops": 0.0})
             k["ms"] += ms[slot]
             k["launches"] += cnt[slot]
             if slot >= 2:
@@ -942,22 +954,14 @@ def main() -> int:
         for slot in range(2 * L + 2 + nu):
             if cnt[slot] == 0:
                 continue
-            name = kernel_name(slot, wl, neck, points=spec is not None)
+            name = slot_kernel(slot, wl, neck, points=spec is not None)
             k = kernels.setdefault(name, {"ms": 0.0, "launches": 0, "flops": 0.0, "bytes": 0.0})
             k["ms"] += ms[slot]
             k["launches"] += cnt[slot]
-            if 2 <= slot < L + 2 or slot >= L + 2 + nu:
-                contraction = slot >= L + 2 + nu
-                l = slot - (L + 1 + nu) if contraction else slot - 1
-                f, b_c, b_s = layer_work(wl, l, act2, pairs2, cnt[slot])
-                if not layer_split(l, wl):
-                    k["flops"] += f
-                    k["bytes"] += b_c + b_s
-                elif contraction:     # the product carries the flops, its operands the bytes
-                    k["flops"] += f
-                    k["bytes"] += b_c
-                else:                 # the tap sum: Z, emitted deltas, lists
-                    k["bytes"] += b_s
+            if 2 <= slot < L + 2:
+                f, b_c, b_s = layer_work(wl, slot - 1, act2, pairs2, cnt[slot])
+                k["flops"] += f
+                k["bytes"] += b_c + b_s
         for name, k in kernels.items():
             log(f"[bench] {name:34s} {k['launches']:5d} launches  avg {k['ms'] / k['launches'] * 1e3:8.2f} us  "
                 f"total {k['ms']:.3f} ms")
@@ -1020,7 +1024,7 @@ def main() -> int:
         fms, fcnt = eng.profile_read()
         eng.profile(False)
         floor = {"stride_us": wall_floor,
-                 "kernels_us": {kernel_name(sl, wl, neck, points=spec is not None): fms[sl] / fcnt[sl] * 1e3
+                 "kernels_us": {slot_kernel(sl, wl, neck, points=spec is not None): fms[sl] / fcnt[sl] * 1e3
                                 for sl in range(len(fcnt)) if fcnt[sl]}}
         log(f"[bench] zero-change stride: {floor['stride_us']:.1f} us; per launch "
             + ", ".join(f"{k} {v:.2f} us" for k, v in floor["kernels_us"].items()))

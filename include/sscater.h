@@ -30,7 +30,10 @@
  *     (a cell's channels are contiguous).
  *   - each layer: 3x3 kernel, zero padding 1, stride 1 or 2, output extent
  *     (n - 1)/stride + 1 per axis; weights OIHW; no bias; optional ReLU.
- *   - dtype SSCATER_F32: fp32 features, weights, maps and accumulation.
+ *   - dtype SSCATER_F32: fp32 features, weights, maps and accumulation; a
+ *     product is formed from 2 x 11-bit halves of either factor (each factor
+ *     to 2^-23 of itself or better, under a common power-of-two scale of 32
+ *     channels).
  *     dtype SSCATER_BF16: bf16 features, weights and layer outputs (round to
  *     nearest even), fp32 accumulation and fp32 pre-activation maps.
  *   - all device pointers are HIP device memory of the calling process.
@@ -325,10 +328,9 @@ int sscater_stats(sscater_t h, sscater_stats_t* out, void* stream);
  * the figure is the kernel's execution time without the event packets' cost.
  * Slots: 0 = input change detection (present pillars; points mode: the pillar
  * queue update), 1 = vanished pillars (points mode: the feature net),
- * 1 + l = layer l (l = 1..L; for a wide stride-1 layer that runs in two
- * launches, its tap sum), L + 2 + u = upsampler u of the neck, and
- * L + 1 + n_ups + l = the contraction launch of layer l when it has one, so
- * 2L + 2 + n_ups slots in all.  Enable it only for runs that measure
+ * 1 + l = layer l (l = 1..L), L + 2 + u = upsampler u of the neck, and
+ * L + 1 + n_ups + l = a second launch of layer l (no layer takes one: these
+ * slots stay zero), so 2L + 2 + n_ups slots in all.  Enable it only for runs that measure
  * kernels. */
 int sscater_profile(sscater_t h, int32_t enable);
 

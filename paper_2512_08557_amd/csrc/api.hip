@@ -32,7 +32,7 @@
 #include <vector>
 
 #include "../../include/sscater.h"
-#include "sscater_internal.h"
+#include "device_common.h"
 
 using namespace ssc;
 
@@ -45,15 +45,13 @@ struct LayerState {
     void* wpack = nullptr;
     uint32_t* stamp = nullptr;
     int32_t* list = nullptr; // NSHARD segments of Hout*Wout cells
-    void* delta = nullptr;   // deltas of this layer's output, dense by cell (nullptr for the last layer)
+    float* wscale = nullptr; // fp32: scale of each output channel's sums
+    void* delta = nullptr;   // delta rows of this layer's output, dense by cell (nullptr for the last layer)
+    uint16_t* dscale = nullptr;   // fp32: their units' scales
     // sparse backbones: the output active-set words (owned by a regular
     // layer, shared with the submanifold layers of its block)
     uint64_t* memb = nullptr;
     bool sub = false;
-    // wide stride-1 layers after the first: two launches, the contraction of
-    // the changed input rows with all nine taps, then the tap sum
-    bool split = false;
-    void* wg = nullptr;      // contraction weights [9*cout][cin]
 };
 
 // One upsampler of the neck.
@@ -63,6 +61,7 @@ struct UpState {
     int Hs = 0, Ws = 0;      // source grid
     int coff = 0;            // first channel in the neck map
     void* wpack = nullptr;
+    float* wscale = nullptr;
 };
 
 thread_local char g_hip_err[256] = "no HIP error";
@@ -92,12 +91,12 @@ struct sscater {
     int Hn = 0, Wn = 0, Cn = 0;
     float* Zn = nullptr;
     uint32_t* stamp_n = nullptr;
-    float* part = nullptr;         // tap contributions of a split layer, dense by cell (shared by those layers)
-    float* zero = nullptr;         // a zero row of 9 * max cout floats
+    void* zero = nullptr;          // a zero delta row
     void* X = nullptr;
     uint64_t* pres = nullptr;
     uint32_t* stamp0 = nullptr;
-    void* delta0 = nullptr;
+    void* delta0 = nullptr;        // input delta rows, dense by cell
+    uint16_t* dscale0 = nullptr;   // fp32: their units' scales
     int32_t* prev[2] = {nullptr, nullptr};
     int prev_slot = 0;
     int32_t prev_count = 0;
@@ -130,7 +129,6 @@ struct sscater {
     uint32_t last_epoch = 0;       // epoch of the last stride
     long long steps = 0;
     int32_t last_pillars = 0;
-    int layer_grid = 1024;
     std::vector<void*> allocs;
     // per-kernel event timing (metrics extension)
     struct ProfRec {
@@ -253,9 +251,13 @@ int run_layers(sscater* h, int set, uint32_t epoch, hipStream_t s) {
         a.cap = (int)h->cells_of(l);
         a.stamp_in = l == 1 ? h->stamp0 : h->layers[l - 2].stamp;
         a.delta_in = l == 1 ? h->delta0 : h->layers[l - 2].delta;
+        a.scale_in = l == 1 ? h->dscale0 : h->layers[l - 2].dscale;
+        a.zero = h->zero;
         a.wpack = ls.wpack;
+        a.wscale = ls.wscale;
         a.Z = ls.Z;
         a.delta_out = ls.delta;   // allocated when a later layer or an upsampler reads it
+        a.scale_out = ls.dscale;
         a.Hin = ls.Hin;
         a.Win = ls.Win;
         a.Hout = ls.Hout;
@@ -279,29 +281,9 @@ int run_layers(sscater* h, int set, uint32_t epoch, hipStream_t s) {
             a.cum_dst = h->cum;
             a.n_cum = h->nlines();
         }
-        if (ls.split) {
-            ContractArgs g{};
-            g.list = h->layers[l - 2].list;
-            g.count = h->cnt_ptr(set, l - 1);
-            g.cap = (int)h->cells_of(l - 1);
-            g.delta_in = a.delta_in;
-            g.wg = ls.wg;
-            g.part = h->part;
-            e = timed_launch(h, h->L + 1 + h->n_ups + l, s, [&](const LaunchCtx& c) {
-                return launch_contract(g, ls.spec.cin, ls.spec.cout, h->bf16, h->layer_grid, c);
-            });
-            if (e != hipSuccess) return hip_fail(e);
-            a.part = h->part;
-            a.zero = h->zero;
-            e = timed_launch(h, 1 + l, s, [&](const LaunchCtx& c) {
-                return launch_tap_sum(a, ls.spec.cout, h->bf16, h->sparse, h->layer_grid, c);
-            });
-        } else {
-            e = timed_launch(h, 1 + l, s, [&](const LaunchCtx& c) {
-                return launch_layer(a, ls.spec.cin, ls.spec.cout, ls.spec.stride, h->bf16, h->sparse, h->layer_grid,
-                                    c);
-            });
-        }
+        e = timed_launch(h, 1 + l, s, [&](const LaunchCtx& c) {
+            return launch_layer(a, ls.spec.cin, ls.spec.cout, ls.spec.stride, h->bf16, h->sparse, c);
+        });
         if (e != hipSuccess) return hip_fail(e);
     }
 
@@ -314,7 +296,9 @@ int run_layers(sscater* h, int set, uint32_t epoch, hipStream_t s) {
         a.count = h->cnt_ptr(set, us.spec.src_layer);
         a.cap = src.Hout * src.Wout;
         a.delta_src = src.delta;
+        a.scale_src = src.dscale;
         a.wpack = us.wpack;
+        a.wscale = us.wscale;
         a.Z = h->Zn;
         a.ctot = h->Cn;
         a.coff = us.coff;
@@ -322,7 +306,7 @@ int run_layers(sscater* h, int set, uint32_t epoch, hipStream_t s) {
         a.Wsrc = us.Ws;
         a.epoch = epoch;
         e = timed_launch(h, h->L + 2 + u, s, [&](const LaunchCtx& c) {
-            return launch_upsample(a, us.cin, us.spec.cout, us.spec.stride, h->bf16, h->layer_grid, c);
+            return launch_upsample(a, us.cin, us.spec.cout, us.spec.stride, h->bf16, c);
         });
         if (e != hipSuccess) return hip_fail(e);
     }
@@ -416,15 +400,6 @@ int create_impl(const sscater_grid* grid, int32_t batch, const sscater_layer* la
     h->L = n_layers;
     h->bf16 = bf16;
     h->row_bytes = row_bytes;
-    // layer launches: 1024 workgroups per image, at most 4096 (a batch of
-    // images carries that many more tiles per launch; measured on four
-    // 1024x1024 images: 4096 workgroups 196 us per stride against 202 us
-    // with 1024); SSCATER_LAYER_GRID overrides it
-    h->layer_grid = (int)std::min<long long>(4096, 1024LL * batch);
-    if (const char* g = getenv("SSCATER_LAYER_GRID")) {
-        const int v = atoi(g);
-        if (v >= 32 && v <= 65536) h->layer_grid = v & ~31;
-    }
     hipError_t he = hipGetDevice(&h->device);
     if (he != hipSuccess) {
         delete h;
@@ -432,12 +407,24 @@ int create_impl(const sscater_grid* grid, int32_t batch, const sscater_layer* la
     }
 
     int rc = SSCATER_OK;
-    const size_t esz = bf16 ? 2 : 4;
-    // SSCATER_FUSED_WIDE=1 keeps every wide stride-1 layer in the one-launch
-    // output-stationary kernel (for comparing the two forms)
-    const char* fw = getenv("SSCATER_FUSED_WIDE");
-    const bool split_wide = !(fw && atoi(fw) != 0);
     const size_t cells = (size_t)cells0;
+    const size_t esz = bf16 ? 2 : 4;
+    // the weights as the caller holds them, one layer at a time, and their
+    // channels' scales, for the packing kernels (freed below)
+    size_t raw_bytes = 0;
+    for (int l = 0; l < n_layers; ++l)
+        raw_bytes = std::max(raw_bytes, (size_t)9 * layers[l].cin * layers[l].cout * esz);
+    for (int u = 0; u < n_ups; ++u)
+        raw_bytes = std::max(raw_bytes, (size_t)layers[ups[u].src_layer - 1].cout * ups[u].cout * ups[u].stride *
+                                            ups[u].stride * esz);
+    void* raw = nullptr;
+    float* fwd = nullptr;
+    he = hipMalloc(&raw, raw_bytes + 256 * sizeof(float));
+    if (he != hipSuccess) {
+        delete h;
+        return hip_fail(he);
+    }
+    fwd = reinterpret_cast<float*>(static_cast<char*>(raw) + raw_bytes);
 #define SSC_TRY(expr)                 \
     do {                              \
         rc = (expr);                  \
@@ -446,15 +433,15 @@ int create_impl(const sscater_grid* grid, int32_t batch, const sscater_layer* la
     SSC_TRY(dev_alloc(h, &h->X, cells * row_bytes));
     SSC_TRY(dev_alloc(h, (void**)&h->pres, cells * 8));
     SSC_TRY(dev_alloc(h, (void**)&h->stamp0, cells * 4));
-    // input deltas dense by cell: fp32 rows or bf16 [new | old] pairs
-    SSC_TRY(dev_alloc(h, &h->delta0, cells * (size_t)(bf16 ? 2 * row_bytes : row_bytes)));
+    SSC_TRY(dev_alloc(h, &h->delta0, cells * delta_row_bytes(grid->C0)));
+    if (!bf16) SSC_TRY(dev_alloc(h, (void**)&h->dscale0, cells * units_of(grid->C0) * 2));
     SSC_TRY(dev_alloc(h, (void**)&h->prev[0], (size_t)grid->max_pillars * 4));
     SSC_TRY(dev_alloc(h, (void**)&h->prev[1], (size_t)grid->max_pillars * 4));
     SSC_TRY(dev_alloc(h, (void**)&h->counters, (size_t)2 * h->ncnt() * 4));
     SSC_TRY(dev_alloc(h, (void**)&h->cum, (size_t)h->ncnt() * 8));
     {
         int H = grid->H, W = grid->W;
-        size_t part_bytes = 0, zero_bytes = 0;
+        size_t zero_bytes = 0;
         for (int l = 0; l < n_layers; ++l) {
             LayerState& ls = h->layers[l];
             ls.spec = layers[l];
@@ -468,34 +455,20 @@ int create_impl(const sscater_grid* grid, int32_t batch, const sscater_layer* la
             SSC_TRY(dev_alloc(h, (void**)&ls.list, oc * 4 * NSHARD));
             bool feeds_up = false;
             for (int u = 0; u < n_ups; ++u) feeds_up = feeds_up || ups[u].src_layer == l + 1;
-            if (l + 1 < n_layers || feeds_up) SSC_TRY(dev_alloc(h, &ls.delta, oc * ls.spec.cout * 4));
-            // the first layer's input list is not built (detection propagates
-            // A_0 straight into A_1), so it always takes the one-launch kernel
-            ls.split = l > 0 && split_wide && contract_supported(ls.spec.cin, ls.spec.cout, ls.spec.stride, bf16);
-            if (ls.split) {
-                const size_t wn = (size_t)9 * ls.spec.cout * ls.spec.cin;
-                std::vector<unsigned char> packed(wn * esz);
-                pack_contract_weights(weights[l], ls.spec.cin, ls.spec.cout, bf16, packed.data());
-                SSC_TRY(dev_alloc(h, &ls.wg, wn * esz));
-                he = hipMemcpy(ls.wg, packed.data(), wn * esz, hipMemcpyHostToDevice);
-                if (he != hipSuccess) { rc = hip_fail(he); goto fail; }
-                part_bytes = std::max(part_bytes, (size_t)batch * H * W * 9 * ls.spec.cout * 4);
-                zero_bytes = std::max(zero_bytes, (size_t)9 * ls.spec.cout * 4);
-            } else {
-                const size_t wn = wpack_elems(ls.spec.cin, ls.spec.cout, bf16);
-                std::vector<unsigned char> packed(wn * esz);
-                pack_weights(weights[l], ls.spec.cin, ls.spec.cout, bf16, packed.data());
-                SSC_TRY(dev_alloc(h, &ls.wpack, wn * esz));
-                he = hipMemcpy(ls.wpack, packed.data(), wn * esz, hipMemcpyHostToDevice);
-                if (he != hipSuccess) { rc = hip_fail(he); goto fail; }
+            if (l + 1 < n_layers || feeds_up) {
+                SSC_TRY(dev_alloc(h, &ls.delta, oc * delta_row_bytes(ls.spec.cout)));
+                if (!bf16) SSC_TRY(dev_alloc(h, (void**)&ls.dscale, oc * units_of(ls.spec.cout) * 2));
             }
+            zero_bytes = std::max(zero_bytes, (size_t)delta_row_bytes(ls.spec.cin));
+            SSC_TRY(dev_alloc(h, &ls.wpack, wpack_bytes(ls.spec.cin, ls.spec.cout, bf16)));
+            if (!bf16) SSC_TRY(dev_alloc(h, (void**)&ls.wscale, (size_t)ls.spec.cout * 4));
+            he = hipMemcpy(raw, weights[l], (size_t)9 * ls.spec.cin * ls.spec.cout * esz, hipMemcpyHostToDevice);
+            if (he == hipSuccess) he = launch_pack_weights(raw, ls.spec.cin, ls.spec.cout, bf16, fwd, ls.wscale, ls.wpack);
+            if (he != hipSuccess) { rc = hip_fail(he); goto fail; }
             H = ls.Hout;
             W = ls.Wout;
         }
-        if (part_bytes) {
-            SSC_TRY(dev_alloc(h, (void**)&h->part, part_bytes));
-            SSC_TRY(dev_alloc(h, (void**)&h->zero, zero_bytes));
-        }
+        SSC_TRY(dev_alloc(h, &h->zero, zero_bytes));
     }
     if (n_ups > 0) {
         h->n_ups = n_ups;
@@ -510,11 +483,12 @@ int create_impl(const sscater_grid* grid, int32_t batch, const sscater_layer* la
             us.Ws = src.Wout;
             us.coff = h->Cn;
             h->Cn += ups[u].cout;
-            const size_t wn = up_wpack_elems(us.cin, ups[u].cout, ups[u].stride, bf16);
-            std::vector<unsigned char> packed(wn * esz);
-            pack_up_weights(up_weights[u], us.cin, ups[u].cout, ups[u].stride, bf16, packed.data());
-            SSC_TRY(dev_alloc(h, &us.wpack, wn * esz));
-            he = hipMemcpy(us.wpack, packed.data(), wn * esz, hipMemcpyHostToDevice);
+            SSC_TRY(dev_alloc(h, &us.wpack, up_wpack_bytes(us.cin, ups[u].cout, ups[u].stride)));
+            if (!bf16) SSC_TRY(dev_alloc(h, (void**)&us.wscale, (size_t)ups[u].cout * 4));
+            he = hipMemcpy(raw, up_weights[u],
+                           (size_t)us.cin * ups[u].cout * ups[u].stride * ups[u].stride * esz, hipMemcpyHostToDevice);
+            if (he == hipSuccess)
+                he = launch_pack_up_weights(raw, us.cin, ups[u].cout, ups[u].stride, bf16, fwd, us.wscale, us.wpack);
             if (he != hipSuccess) { rc = hip_fail(he); goto fail; }
         }
         SSC_TRY(dev_alloc(h, (void**)&h->Zn, (size_t)Hn * Wn * h->Cn * 4));
@@ -528,10 +502,12 @@ int create_impl(const sscater_grid* grid, int32_t batch, const sscater_layer* la
     he = hipDeviceSynchronize();
     if (he != hipSuccess) { rc = hip_fail(he); goto fail; }
 #undef SSC_TRY
+    (void)hipFree(raw);
     h->epoch = 0;
     *out = h;
     return SSCATER_OK;
 fail:
+    (void)hipFree(raw);
     free_all(h);
     delete h;
     return rc;
@@ -587,6 +563,7 @@ static int step_impl(sscater_t h, const sscater_pillars* pl, void* stream, bool 
     d.stamp0 = h->stamp0;
     d.count0 = h->a0_ptr(set);
     d.delta0 = h->delta0;
+    d.scale0 = h->dscale0;
     d.zero_ptr = h->set_ptr(set ^ 1);
     d.zero_n = h->nlines();
     d.HW = (int32_t)cells;
@@ -766,6 +743,7 @@ int sscater_step_points(sscater_t h, const float* points, int32_t n_points, void
     f.res = p.res;
     f.X = h->X;
     f.delta0 = h->delta0;
+    f.scale0 = h->dscale0;
     f.tcount_clear = h->tcount + (size_t)pop * CSTRIDE;   // the next stride inserts into this slot
     f.err = h->err_dev;
     f.epoch = epoch;

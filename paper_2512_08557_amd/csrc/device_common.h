@@ -268,44 +268,156 @@ __device__ __forceinline__ uint32_t f32_to_bf16_bits(float f) {
     return u >> 16;
 }
 
-// Z update and next-layer delta row of one lane: output cell q, output
-// channels co0 .. co0+3 (fp32 Z_new = Z_old + D; delta phi(Z_new) -
-// phi(Z_old), or the bf16 pair [bf16(phi(Z_new)) | bf16(phi(Z_old))]).
+// ---- delta rows ----
+//
+// A delta row is stored at its cell in units of 32 channels, 128 bytes each:
+// two planes of 32 16-bit values, so that one unit is both planes of one
+// K = 32 matrix instruction and a row has 4 bytes per channel in either dtype.
+// Rows of fewer than 32 channels take one unit whose other values stay zero.
+//   bf16: plane 0 holds bf16(phi(Z_new)), plane 1 bf16(phi(Z_old)); the
+//         consumers contract the difference of the two exactly.
+//   fp32: plane 0 holds hi = fp16(v * s), plane 1 lo = fp16(v * s - hi), where
+//         v is the fp32 delta and s the power of two that brings the unit's
+//         largest |v| into [2^14, 2^15); the unit's 1/s is kept beside the
+//         rows as a bf16 value (a power of two, so exact).  hi + lo carries v
+//         to 2^-24 of itself, half an fp32 ulp (2^-39 of the unit's largest
+//         value where that is more), and the weights are split the same way
+//         with a scale per output channel, so hi*hi + lo*hi + hi*lo on the
+//         fp16 matrix cores stands for the fp32 product at 3 matrix
+//         instructions per 32 channels instead of 8 of the fp32 kind.  Scales
+//         multiply fp32 sums only, by powers of two.
+//         A row of 16 channels leaves half of its unit free, which takes what
+//         the split leaves over (rest = v * s - hi - lo, at no cost to the
+//         consumers): plane 0 = [hi | rest], plane 1 = [lo | hi], against the
+//         weights' planes [Whi | Wrest] and [Wlo | Whi].  The short sums of 16
+//         channels are the ones where the split's error would show (3e-8 of
+//         the result beside the 9e-8 of the fp32 arithmetic around it).
+// A unit that holds a NaN or an infinity gets that as its 1/s (and +-1 at the
+// infinite values), so that what it contributes is not finite either.
+constexpr int UNIT_BYTES = 128;
+__host__ __device__ constexpr int units_of(int channels) { return channels > 32 ? channels / 32 : 1; }
+__host__ __device__ constexpr int delta_row_bytes(int channels) { return units_of(channels) * UNIT_BYTES; }
+
+typedef _Float16 h8v __attribute__((ext_vector_type(8)));
+typedef _Float16 h4v __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ uint32_t abs_bits4(const f4v v) {
+    return max(max(__float_as_uint(v.x) & 0x7FFFFFFFu, __float_as_uint(v.y) & 0x7FFFFFFFu),
+               max(__float_as_uint(v.z) & 0x7FFFFFFFu, __float_as_uint(v.w) & 0x7FFFFFFFu));
+}
+
+// Scale of a unit whose largest |value| has the bits mb: the factor s, and
+// the bf16 bits of 1/s.
+struct UnitScale {
+    float s;
+    uint16_t inv;
+    bool finite;
+};
+__device__ __forceinline__ UnitScale unit_scale(uint32_t mb) {
+    UnitScale u;
+    const int e = (int)(mb >> 23);                    // biased exponent of the largest value
+    u.finite = e != 255;
+    const int se = min(268 - e, 253);                 // s = 2^(se - 127), 1/s a normal number
+    u.s = __uint_as_float((uint32_t)se << 23);
+    u.inv = (uint16_t)(u.finite ? (254 - se) << 7 : (mb > 0x7F800000u ? 0x7FC0 : 0x7F80));
+    return u;
+}
+
+// hi, lo and rest of a value under its unit's scale.
+__device__ __forceinline__ void split1(float v, const UnitScale& u, _Float16& hi, _Float16& lo, _Float16& rest) {
+    float t = v * u.s;
+    if (!u.finite) t = __builtin_isinf(v) ? copysignf(1.f, v) : 0.f;
+    hi = (_Float16)t;
+    lo = (_Float16)(t - (float)hi);
+    rest = (_Float16)(t - (float)hi - (float)lo);
+}
+
+// Four consecutive channels of a row of C channels into their places (p: the
+// first one's in plane 0).
+template <int C>
+__device__ __forceinline__ void store_split4(char* p, const f4v v, const UnitScale& u, bool store) {
+    h4v h, l, r;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        _Float16 x, y, z;
+        split1(v[k], u, x, y, z);
+        h[k] = x;
+        l[k] = y;
+        r[k] = z;
+    }
+    if (!store) return;
+    *reinterpret_cast<h4v*>(p) = h;
+    *reinterpret_cast<h4v*>(p + 64) = l;
+    if constexpr (C == 16) {
+        *reinterpret_cast<h4v*>(p + 32) = r;
+        *reinterpret_cast<h4v*>(p + 96) = h;
+    }
+}
+
+__device__ __forceinline__ float bf16_to_f32(uint32_t b) { return __uint_as_float(b << 16); }
+
+// Z update and next-layer delta row of one lane: output cell q, NBL blocks of
+// 16 output channels from channel c0 on, of which the lane holds the four at
+// 4*g (Z_new = Z_old + D; delta phi(Z_new) - phi(Z_old), see above).  The NBL
+// blocks are one unit (or all of a row of fewer than 32 channels), and the
+// lanes l, l^16, l^32, l^48 hold its channels of one cell: every lane of the
+// wavefront calls this, `store` says whether its cell and channels exist.
 // Sparse backbones: now / prev say whether the site is active in this and
 // in the previous stride; an inactive site's output is zero.
-template <int COUT, bool BF16>
-__device__ __forceinline__ void epilogue4(const LayerArgs& a, int q, int co0, const f4v o, const f4v d,
-                                          bool now = true, bool prev = true) {
-    f4v zn;
-    zn.x = o.x + d.x;
-    zn.y = o.y + d.y;
-    zn.z = o.z + d.z;
-    zn.w = o.w + d.w;
-    *reinterpret_cast<f4v*>(a.Z + (size_t)q * COUT + co0) = zn;
-    if (!a.delta_out) return;
-    f4v yo = o, yn = zn;
-    if (a.relu) {
-        yo.x = fmaxf(yo.x, 0.f); yo.y = fmaxf(yo.y, 0.f); yo.z = fmaxf(yo.z, 0.f); yo.w = fmaxf(yo.w, 0.f);
-        yn.x = fmaxf(yn.x, 0.f); yn.y = fmaxf(yn.y, 0.f); yn.z = fmaxf(yn.z, 0.f); yn.w = fmaxf(yn.w, 0.f);
+template <int COUT, bool BF16, int NBL>
+__device__ __forceinline__ void epilogue_unit(const LayerArgs& a, int q, int c0, int g, const f4v (&o)[NBL],
+                                              const f4v (&d)[NBL], bool store, bool now, bool prev) {
+    f4v yo[NBL], yn[NBL];
+#pragma unroll
+    for (int i = 0; i < NBL; ++i) {
+        f4v zn;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) zn[k] = o[i][k] + d[i][k];
+        if (store) *reinterpret_cast<f4v*>(a.Z + (size_t)q * COUT + c0 + i * 16 + 4 * g) = zn;
+        yo[i] = o[i];
+        yn[i] = zn;
+        if (a.relu) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                yo[i][k] = fmaxf(yo[i][k], 0.f);
+                yn[i][k] = fmaxf(yn[i][k], 0.f);
+            }
+        }
+        if (!prev) yo[i] = f4v{0.f, 0.f, 0.f, 0.f};
+        if (!now) yn[i] = f4v{0.f, 0.f, 0.f, 0.f};
     }
-    if (!prev) yo = f4v{0.f, 0.f, 0.f, 0.f};
-    if (!now) yn = f4v{0.f, 0.f, 0.f, 0.f};
-    char* drow = static_cast<char*>(a.delta_out) + (size_t)q * (4 * COUT);
+    if (!a.delta_out) return;                         // uniform
+    const int u = c0 / 32;
+    char* unit = static_cast<char*>(a.delta_out) + (size_t)q * delta_row_bytes(COUT) + u * UNIT_BYTES +
+                 (c0 % 32) * 2 + g * 8;
     if constexpr (BF16) {
-        uint2 pn, po;
-        pn.x = f32_to_bf16_bits(yn.x) | (f32_to_bf16_bits(yn.y) << 16);
-        pn.y = f32_to_bf16_bits(yn.z) | (f32_to_bf16_bits(yn.w) << 16);
-        po.x = f32_to_bf16_bits(yo.x) | (f32_to_bf16_bits(yo.y) << 16);
-        po.y = f32_to_bf16_bits(yo.z) | (f32_to_bf16_bits(yo.w) << 16);
-        *reinterpret_cast<uint2*>(drow + co0 * 2) = pn;
-        *reinterpret_cast<uint2*>(drow + COUT * 2 + co0 * 2) = po;
+#pragma unroll
+        for (int i = 0; i < NBL; ++i) {
+            uint2 pn, po;
+            pn.x = f32_to_bf16_bits(yn[i].x) | (f32_to_bf16_bits(yn[i].y) << 16);
+            pn.y = f32_to_bf16_bits(yn[i].z) | (f32_to_bf16_bits(yn[i].w) << 16);
+            po.x = f32_to_bf16_bits(yo[i].x) | (f32_to_bf16_bits(yo[i].y) << 16);
+            po.y = f32_to_bf16_bits(yo[i].z) | (f32_to_bf16_bits(yo[i].w) << 16);
+            if (store) {
+                *reinterpret_cast<uint2*>(unit + i * 32) = pn;
+                *reinterpret_cast<uint2*>(unit + 64 + i * 32) = po;
+            }
+        }
     } else {
-        f4v dy;
-        dy.x = yn.x - yo.x;
-        dy.y = yn.y - yo.y;
-        dy.z = yn.z - yo.z;
-        dy.w = yn.w - yo.w;
-        *reinterpret_cast<f4v*>(drow + co0 * 4) = dy;
+        f4v dy[NBL];
+        uint32_t mb = 0u;
+#pragma unroll
+        for (int i = 0; i < NBL; ++i) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) dy[i][k] = yn[i][k] - yo[i][k];
+            mb = max(mb, abs_bits4(dy[i]));
+        }
+        mb = max(mb, (uint32_t)__shfl_xor((int)mb, 16));
+        mb = max(mb, (uint32_t)__shfl_xor((int)mb, 32));
+        const UnitScale us = unit_scale(mb);
+#pragma unroll
+        for (int i = 0; i < NBL; ++i) store_split4<COUT>(unit + i * 32, dy[i], us, store);
+        if (store && g == 0) a.scale_out[(size_t)q * units_of(COUT) + u] = us.inv;
     }
 }
 
@@ -334,25 +446,25 @@ __device__ __forceinline__ void lds_barrier() {
     asm volatile("" ::: "memory");
 }
 
-// wait_vm for a count known once the chunk loop is unrolled
+// wait_vm for a count that is a constant once its loop is unrolled (at most N)
+template <int N>
 __device__ __forceinline__ void wait_vm_n(int n) {
-    switch (n) {
-        case 0: wait_vm<0>(); break;
-        case 4: wait_vm<4>(); break;
-        case 6: wait_vm<6>(); break;
-        case 8: wait_vm<8>(); break;
-        case 12: wait_vm<12>(); break;
-        case 16: wait_vm<16>(); break;
-        case 18: wait_vm<18>(); break;
-        case 24: wait_vm<24>(); break;
-        case 32: wait_vm<32>(); break;
-        default: wait_vm<0>(); break;
-    }
+    if (n >= N) wait_vm<N>();
+    else if constexpr (N > 0) wait_vm_n<N - 1>(n);
 }
 
-__device__ __forceinline__ void copy16(const void* src, void* lds) {
+typedef __attribute__((address_space(3))) char lds_char;
+
+// 16 bytes per lane from global memory straight into LDS (lane l to lds + 16*l)
+__device__ __forceinline__ void copy16(const void* src, lds_char* lds) {
     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
                                      (__attribute__((address_space(3))) void*)lds, 16, 0, 0);
+}
+
+__device__ __forceinline__ uint4 lds16(const lds_char* p) {
+    typedef uint32_t u4v __attribute__((ext_vector_type(4)));
+    const u4v v = *reinterpret_cast<const __attribute__((address_space(3))) u4v*>(p);
+    return make_uint4(v.x, v.y, v.z, v.w);
 }
 
 __device__ __forceinline__ void flag_error(int32_t* err, int bit) {

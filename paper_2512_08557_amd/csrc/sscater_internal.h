@@ -77,7 +77,8 @@ struct DetectArgs {
     int32_t chk_count;
     uint32_t* stamp0;     // change stamps of the input grid [H0*W0]
     int32_t* count0;      // |A_0| (statistics only): segment k, XCD x at count0[(k * PSPREAD + x) * CSTRIDE]
-    void* delta0;         // input deltas, dense by cell [H0*W0][4*C0 bytes]
+    void* delta0;         // input delta rows, dense by cell
+    uint16_t* scale0;     // fp32: their units' scales, dense by cell [H0*W0][units]
     int32_t* zero_ptr;    // counters to clear for the next stride (may be nullptr)
     int32_t zero_n;       // their lines (word 0 of each CSTRIDE line is the counter)
     int32_t HW;
@@ -89,16 +90,21 @@ struct DetectArgs {
 
 // One convolution layer: contraction of the input deltas with the weights,
 // update of the persistent pre-activation map, activation delta epilogue and
-// propagation of the change list to the next layer.
+// propagation of the change list to the next layer.  Delta rows and their
+// scales: see device_common.h.
 struct LayerArgs {
     const int32_t* list;        // A_l: NSHARD segments of `cap` cells of the output grid
     const int32_t* count;       // segment lengths, segment k at count[k * CSTRIDE]
     int cap;                    // capacity of a segment (cells of the output grid)
     const uint32_t* stamp_in;   // change stamps of the input grid [Hin*Win]
-    const void* delta_in;       // input deltas, dense by cell [Hin*Win][4*cin bytes]
+    const void* delta_in;       // input delta rows, dense by cell
+    const uint16_t* scale_in;   // fp32: their units' scales [Hin*Win][units]
+    const void* zero;           // a zero row, read for an unchanged input
     const void* wpack;          // weights repacked for the MFMA operand layout
+    const float* wscale;        // fp32: scale of each output channel's sums
     float* Z;                   // persistent pre-activation map [Hout*Wout][cout]
-    void* delta_out;            // output deltas, dense by cell (nullptr: last layer)
+    void* delta_out;            // output delta rows, dense by cell (nullptr: last layer)
+    uint16_t* scale_out;        // fp32: their units' scales
     int Hin, Win, Hout, Wout;
     int relu;
     uint32_t epoch;
@@ -112,23 +118,6 @@ struct LayerArgs {
     const int32_t* cum_src;     // this stride's counters, word 0 of n_cum CSTRIDE lines
     long long* cum_dst;         // totals, the same layout
     int n_cum;
-    // layers contracted in two launches (tap_sum_kernel): the tap
-    // contributions of the changed input cells, dense by cell
-    // [Hin*Win][9][cout] fp32, and a zero row of 9*cout floats that stands
-    // in for an unchanged input
-    const float* part;
-    const float* zero;
-};
-
-// The scatter form of Eq. 2 for one stride-1 layer: every changed input row
-// times the weights of all nine taps, [|A_{l-1}| x cin] x [cin x 9*cout].
-struct ContractArgs {
-    const int32_t* list;        // A_{l-1}: NSHARD segments of `cap` cells of the input grid
-    const int32_t* count;       // segment lengths, segment k at count[k * CSTRIDE]
-    int cap;
-    const void* delta_in;       // input deltas, dense by cell [Hin*Win][4*cin bytes]
-    const void* wg;             // weights [9*cout][cin] (fp32, or bf16 values), row tap*cout + co
-    float* part;                // tap contributions, dense by cell [Hin*Win][9*cout]
 };
 
 // One upsampler of the neck: transposed convolution (kernel = stride) of a
@@ -137,8 +126,10 @@ struct UpArgs {
     const int32_t* list;        // the source layer's change list: NSHARD segments of `cap` cells
     const int32_t* count;       // segment lengths, segment k at count[k * CSTRIDE]
     int cap;                    // cells of the source grid
-    const void* delta_src;      // source deltas, dense by cell [Hsrc*Wsrc][4*cin bytes]
+    const void* delta_src;      // source delta rows, dense by cell
+    const uint16_t* scale_src;  // fp32: their units' scales
     const void* wpack;          // weights repacked for the MFMA operand layout
+    const float* wscale;        // fp32: scale of each output channel's sums
     float* Z;                   // neck pre-activation map [Hn*Wn][ctot]
     int ctot, coff;             // channels of the neck map, first channel of this upsampler
     uint32_t* stamp;            // change stamps of the neck grid [Hn*Wn]
@@ -191,7 +182,8 @@ struct PfnArgs {
     int C0, W;
     float x_min, y_min, res;
     void* X;                    // canvas [H*W][C0] (grid dtype)
-    void* delta0;               // input deltas dense by cell
+    void* delta0;               // input delta rows, dense by cell
+    uint16_t* scale0;           // fp32: their units' scales
     int32_t* tcount_clear;      // counter of the next stride's insertion slot, cleared here
     int32_t* err;
     uint32_t epoch;
@@ -238,8 +230,7 @@ hipError_t launch_detect_present(const DetectArgs& a, int row_bytes, bool bf16, 
 hipError_t launch_detect_vanished(const DetectArgs& a, int row_bytes, bool bf16, const LaunchCtx& c);
 hipError_t launch_detect_sorted(const DetectArgs& a, int row_bytes, bool bf16, const LaunchCtx& c);
 bool layer_supported(int cin, int cout, int stride, bool bf16);
-hipError_t launch_layer(const LayerArgs& a, int cin, int cout, int stride, bool bf16, bool sparse, int grid,
-                        const LaunchCtx& c);
+hipError_t launch_layer(const LayerArgs& a, int cin, int cout, int stride, bool bf16, bool sparse, const LaunchCtx& c);
 hipError_t launch_read(const float* Z, void* dst, long long n, int relu, bool bf16, hipStream_t s);
 // phi(Z) with the sites outside the active set (sparse backbones) zeroed.
 hipError_t launch_read_masked(const float* Z, void* dst, long long cells, int cout, const uint64_t* memb, int relu,
@@ -248,27 +239,19 @@ hipError_t launch_read_masked(const float* Z, void* dst, long long cells, int co
 // channels of a [cells][ctot] destination.
 hipError_t launch_read_slice(const float* Z, void* dst, long long cells, int ctot, int coff, int cout, int relu,
                              bool bf16, hipStream_t s);
-// Wide stride-1 layers: the contraction of the changed input rows with all
-// nine taps into `part`, then the output-stationary sum of the tap
-// contributions with the Z update, the delta epilogue and the propagation.
-bool contract_supported(int cin, int cout, int stride, bool bf16);
-hipError_t launch_contract(const ContractArgs& a, int cin, int cout, bool bf16, int grid, const LaunchCtx& c);
-hipError_t launch_tap_sum(const LayerArgs& a, int cout, bool bf16, bool sparse, int grid, const LaunchCtx& c);
-// [9*cout][cin] contraction weights from OIHW (fp32 values, or bf16 bits).
-void pack_contract_weights(const void* w_oihw, int cin, int cout, bool bf16, void* dst);
 bool upsample_supported(int cin, int cout, int stride);
-hipError_t launch_upsample(const UpArgs& a, int cin, int cout, int stride, bool bf16, int grid,
-                           const LaunchCtx& c);
-size_t up_wpack_elems(int cin, int cout, int stride, bool bf16);
-// Repack [cin][cout][S][S] transposed-conv weights (fp32 values, or bf16 bits)
-// into the layout the upsampling kernel reads.
-void pack_up_weights(const void* w, int cin, int cout, int stride, bool bf16, void* dst);
+hipError_t launch_upsample(const UpArgs& a, int cin, int cout, int stride, bool bf16, const LaunchCtx& c);
+// Weights in the layouts the kernels read (see layer.hip), packed on the device
+// (null stream) from the caller's: OIHW, or [cin][cout][S][S] of an upsampler.
+// fwd: cout floats of scratch, inv: what each output channel's sums are
+// multiplied by (both fp32 only); out: zeroed.
+size_t wpack_bytes(int cin, int cout, bool bf16);
+size_t up_wpack_bytes(int cin, int cout, int stride);
+hipError_t launch_pack_weights(const void* w, int cin, int cout, bool bf16, float* fwd, float* inv, void* out);
+hipError_t launch_pack_up_weights(const void* w, int cin, int cout, int stride, bool bf16, float* fwd, float* inv,
+                                  void* out);
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s);
 hipError_t launch_pillar_update(const PillarArgs& a, int insert_blocks, const LaunchCtx& c);
 hipError_t launch_pfn(const PfnArgs& a, bool bf16, int blocks, const LaunchCtx& c);
-size_t wpack_elems(int cin, int cout, bool bf16);
-// Repack OIHW weights (fp32 values, or bf16 bit patterns) into the layout the
-// layer kernel reads; dst holds wpack_elems() elements of 4 (fp32) or 2 (bf16) bytes.
-void pack_weights(const void* w_oihw, int cin, int cout, bool bf16, void* dst);
 
 }  // namespace ssc

@@ -27,8 +27,8 @@ namespace ssc {
 
 template <int CIN, int COUT, int S, bool BF16>
 struct UpShape {
-    static constexpr int KTOT = BF16 ? 2 * CIN : CIN;
-    static constexpr int NCH = KTOT / (BF16 ? 32 : 16);   // 1 KB operand chunks
+    static constexpr int NU = units_of(CIN);
+    static constexpr int NCH = 2 * NU;                    // 1 KB operand chunks: both planes of every unit
     static constexpr int NCBT = COUT / 16;
     static constexpr int NOB = S * S * NCBT;              // output blocks per input cell
     static constexpr int BPW = NOB >= 8 ? 2 : 1;          // output blocks per wavefront
@@ -39,7 +39,7 @@ template <int CIN, int COUT, int S, bool BF16>
 __global__ __launch_bounds__(256) void upsample_kernel(UpArgs a) {
     using U = UpShape<CIN, COUT, S, BF16>;
     constexpr int NCH = U::NCH, NOB = U::NOB, NCBT = U::NCBT, BPW = U::BPW, OBG = U::OBG;
-    constexpr int ROWB = 4 * CIN;                          // delta row bytes (fp32, or bf16 pair)
+    constexpr int NU = U::NU, ROWB = delta_row_bytes(CIN);
     __shared__ uint4 As0[NCH][64];
     __shared__ uint4 As1[NCH][64];
 
@@ -94,7 +94,19 @@ __global__ __launch_bounds__(256) void upsample_kernel(UpArgs a) {
     };
     int tile = (b / OBG) / NSHARD;
     int pc = 0, pn = 0;        // cells of this lane's row in this tile and the next
-    f4v zo[BPW];
+    f4v zo[BPW], wsc[BPW];
+    // fp32: the row's unit scales (two per word; one unit: the low half)
+    constexpr int SW = BF16 ? 1 : (NU + 1) / 2;
+    uint32_t sc[SW] = {};
+    auto scales = [&](int p, uint32_t (&s)[SW]) __attribute__((always_inline)) {
+        if constexpr (!BF16) {
+            const uint16_t* sp = a.scale_src + (size_t)p * NU;
+            if constexpr (NU == 1) s[0] = *sp;
+            else
+#pragma unroll
+                for (int i = 0; i < SW; ++i) s[i] = reinterpret_cast<const uint32_t*>(sp)[i];
+        }
+    };
     if (tile * 16 < n) {
         pc = entry(tile);
 #pragma unroll
@@ -104,6 +116,11 @@ __global__ __launch_bounds__(256) void upsample_kernel(UpArgs a) {
                 (__attribute__((address_space(3))) void*)&As0[c][0], 16, 0, 0);
 #pragma unroll
         for (int k = 0; k < BPW; ++k) zo[k] = *reinterpret_cast<const f4v*>(z_at(out_cell(pc, k), k));
+        scales(pc, sc);
+        if constexpr (!BF16)
+#pragma unroll
+            for (int k = 0; k < BPW; ++k)
+                wsc[k] = *reinterpret_cast<const f4v*>(a.wscale + (ob[k] - (ob[k] / NCBT) * NCBT) * 16 + 4 * g);
         pn = entry(tile + TG);
     }
     // one tile from `cur`, the next one's rows into `nxt`; false past the end
@@ -114,6 +131,7 @@ __global__ __launch_bounds__(256) void upsample_kernel(UpArgs a) {
         __syncthreads();                                   // this tile's chunks have landed; `nxt` is free
         const bool more = (tile + TG) * 16 < n;
         f4v zn_next[BPW];
+        uint32_t sc_next[SW] = {};
         int pnn = 0;
         if (more) {
 #pragma unroll
@@ -123,29 +141,50 @@ __global__ __launch_bounds__(256) void upsample_kernel(UpArgs a) {
                     (__attribute__((address_space(3))) void*)&nxt[c][0], 16, 0, 0);
 #pragma unroll
             for (int k = 0; k < BPW; ++k) zn_next[k] = *reinterpret_cast<const f4v*>(z_at(out_cell(pn, k), k));
+            scales(pn, sc_next);
             pnn = entry(tile + 2 * TG);
         }
         f4v acc[BPW];
 #pragma unroll
         for (int k = 0; k < BPW; ++k) acc[k] = f4v{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int c = 0; c < NCH; ++c) {
-            const uint4 av = cur[c][lane];
+        for (int u = 0; u < NU; ++u) {
+            const uint4 av = cur[2 * u][lane], ov = cur[2 * u + 1][lane];
+            if constexpr (BF16) {
+                bf8v A, O;
+                __builtin_memcpy(&A, &av, 16);
+                __builtin_memcpy(&O, &ov, 16);
 #pragma unroll
-            for (int k = 0; k < BPW; ++k) {
-                if constexpr (BF16) {
-                    bf8v A, B;
-                    __builtin_memcpy(&A, &bw[k][c], 16);
-                    __builtin_memcpy(&B, &av, 16);
-                    acc[k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, B, acc[k], 0, 0, 0);
-                } else {
-                    acc[k] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(bw[k][c].x), __uint_as_float(av.x), acc[k], 0, 0, 0);
-                    acc[k] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(bw[k][c].y), __uint_as_float(av.y), acc[k], 0, 0, 0);
-                    acc[k] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(bw[k][c].z), __uint_as_float(av.z), acc[k], 0, 0, 0);
-                    acc[k] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(bw[k][c].w), __uint_as_float(av.w), acc[k], 0, 0, 0);
+                for (int k = 0; k < BPW; ++k) {
+                    bf8v B, N;
+                    __builtin_memcpy(&B, &bw[k][2 * u], 16);
+                    __builtin_memcpy(&N, &bw[k][2 * u + 1], 16);
+                    acc[k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(B, A, acc[k], 0, 0, 0);
+                    acc[k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(N, O, acc[k], 0, 0, 0);
+                }
+            } else {
+                h8v A, O;
+                __builtin_memcpy(&A, &av, 16);
+                __builtin_memcpy(&O, &ov, 16);
+                const float s = bf16_to_f32((sc[u / 2] >> (16 * (u & 1))) & 0xFFFFu);
+#pragma unroll
+                for (int k = 0; k < BPW; ++k) {
+                    h8v H, Lw;
+                    __builtin_memcpy(&H, &bw[k][2 * u], 16);
+                    __builtin_memcpy(&Lw, &bw[k][2 * u + 1], 16);
+                    f4v P = __builtin_amdgcn_mfma_f32_16x16x32_f16(Lw, A, f4v{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+                    P = __builtin_amdgcn_mfma_f32_16x16x32_f16(H, O, P, 0, 0, 0);
+                    P = __builtin_amdgcn_mfma_f32_16x16x32_f16(H, A, P, 0, 0, 0);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) acc[k][j] = fmaf(P[j], s, acc[k][j]);
                 }
             }
         }
+        if constexpr (!BF16)
+#pragma unroll
+            for (int k = 0; k < BPW; ++k)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) acc[k][j] *= wsc[k][j];
         if (vrow) {
 #pragma unroll
             for (int k = 0; k < BPW; ++k) {
@@ -163,6 +202,8 @@ __global__ __launch_bounds__(256) void upsample_kernel(UpArgs a) {
         if (more) {
 #pragma unroll
             for (int k = 0; k < BPW; ++k) zo[k] = zn_next[k];
+#pragma unroll
+            for (int i = 0; i < SW; ++i) sc[i] = sc_next[i];
         }
         pc = pn;
         pn = pnn;
@@ -186,69 +227,23 @@ bool upsample_supported(int cin, int cout, int stride) {
 }
 
 template <int CI, int CO, int S, bool BF16>
-static hipError_t launch_up_shape(const UpArgs& a, int grid, const LaunchCtx& c) {
+static hipError_t launch_up_shape(const UpArgs& a, const LaunchCtx& c) {
     using U = UpShape<CI, CO, S, BF16>;
     // tile slots per (segment, block group), about two workgroups per compute
     // unit in all (a workgroup keeps its weights over its tiles); at most
     // ceil(cap / 16) tiles per segment
-    (void)grid;
     int tg = std::max(1, 512 / (U::OBG * NSHARD));
     tg = std::min(tg, std::max(1, (a.cap + 15) / 16));
     return launch_kernel(c, upsample_kernel<CI, CO, S, BF16>, dim3(tg * U::OBG * NSHARD), dim3(256), a);
 }
 
-hipError_t launch_upsample(const UpArgs& a, int cin, int cout, int stride, bool bf16, int grid,
-                           const LaunchCtx& c) {
+hipError_t launch_upsample(const UpArgs& a, int cin, int cout, int stride, bool bf16, const LaunchCtx& c) {
 #define SSC_LAUNCH(CI, CO, S)                                                                               \
     if (cin == CI && cout == CO && stride == S)                                                             \
-        return bf16 ? launch_up_shape<CI, CO, S, true>(a, grid, c) : launch_up_shape<CI, CO, S, false>(a, grid, c);
+        return bf16 ? launch_up_shape<CI, CO, S, true>(a, c) : launch_up_shape<CI, CO, S, false>(a, c);
     SSC_UP_SHAPES(SSC_LAUNCH)
 #undef SSC_LAUNCH
     return hipErrorInvalidValue;
-}
-
-size_t up_wpack_elems(int cin, int cout, int stride, bool bf16) {
-    return (size_t)(bf16 ? 2 * cin : cin) * (size_t)cout * stride * stride;
-}
-
-// Layout, in 16-byte lane vectors: [chunk c][output block ob][lane l], with
-// ob = (a*S + b)*NCBT + cb; lane l of block ob holds output channel
-// cb*16 + l%16 of sub-cell (a, b) and the k-group l/16 of chunk c: fp32
-// k = c*16 + 4*(l/16) + e (e < 4); bf16 k = c*32 + 8*(l/16) + e (e < 8) over
-// the pair [W | -W].  w: [cin][cout][S][S] (fp32 values, or bf16 bits).
-void pack_up_weights(const void* w, int cin, int cout, int s, bool bf16, void* dst) {
-    const int ncbt = cout / 16, nob = s * s * ncbt;
-    auto widx = [&](int ci, int co, int a, int b) { return (((size_t)ci * cout + co) * s + a) * s + b; };
-    if (!bf16) {
-        const float* src = static_cast<const float*>(w);
-        float* out = static_cast<float*>(dst);
-        const int nch = cin / 16;
-        for (int c = 0; c < nch; ++c)
-            for (int ob = 0; ob < nob; ++ob) {
-                const int ab = ob / ncbt, cb = ob % ncbt;
-                for (int l = 0; l < 64; ++l)
-                    for (int e = 0; e < 4; ++e) {
-                        const int co = cb * 16 + l % 16, ci = c * 16 + 4 * (l / 16) + e;
-                        out[(((size_t)c * nob + ob) * 64 + l) * 4 + e] = src[widx(ci, co, ab / s, ab % s)];
-                    }
-            }
-    } else {
-        const uint16_t* src = static_cast<const uint16_t*>(w);
-        uint16_t* out = static_cast<uint16_t*>(dst);
-        const int nch = (2 * cin) / 32;
-        for (int c = 0; c < nch; ++c)
-            for (int ob = 0; ob < nob; ++ob) {
-                const int ab = ob / ncbt, cb = ob % ncbt;
-                for (int l = 0; l < 64; ++l)
-                    for (int e = 0; e < 8; ++e) {
-                        const int co = cb * 16 + l % 16, k = c * 32 + 8 * (l / 16) + e;
-                        const int ci = k < cin ? k : k - cin;
-                        uint16_t v = src[widx(ci, co, ab / s, ab % s)];
-                        if (k >= cin) v ^= 0x8000u;   // -W: exact sign flip
-                        out[(((size_t)c * nob + ob) * 64 + l) * 8 + e] = v;
-                    }
-            }
-    }
 }
 
 }  // namespace ssc
