@@ -267,12 +267,12 @@ def cpu_baseline_points(wl, ws, spec, pw, batches, first, budget_s):
 # scaled by what the same counters read for a plain copy of known size.
 # --------------------------------------------------------------------------
 KERNEL_SOURCES = ("detect.hip", "layer.hip", "misc.hip", "upsample.hip", "pfn.hip",
-                  "device_common.h", "sscater_internal.h")
+                  "plan.h", "device_common.h", "sscater_internal.h")
 
 
 # the device-code sources each kernel family is built from
 KERNEL_FILES = {
-    "layer_kernel": ("layer.hip", "device_common.h", "sscater_internal.h"),
+    "layer_kernel": ("layer.hip", "plan.h", "device_common.h", "sscater_internal.h"),
     "detect_kernel": ("detect.hip", "device_common.h", "sscater_internal.h"),
     "detect_sorted_kernel": ("detect.hip", "device_common.h", "sscater_internal.h"),
     "upsample_kernel": ("upsample.hip", "device_common.h", "sscater_internal.h"),

@@ -2,8 +2,8 @@
 
 Every HIP translation unit under csrc/ is compiled separately (in parallel)
 and linked into one shared library next to this file.  Packed-FP32 VALU
-instructions are disabled for all device code; the first five SGPRs of
-kernel arguments are preloaded (gfx950 kernarg preloading).
+instructions are disabled for all device code; leading scalar kernel
+arguments are preloaded into SGPRs (gfx950 kernarg preloading).
 """
 from __future__ import annotations
 
@@ -23,9 +23,10 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 COMMON = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-    # the layer kernels' leading (list, count, cap) arguments arrive in SGPRs,
-    # so their first loads need not wait for the kernel-argument fetch
-    "-mllvm", "-amdgpu-kernarg-preload-count=5",
+    # the layer kernels' leading scalar arguments (list, counts, tap bits,
+    # weights) arrive in SGPRs, so their first loads need not wait for the
+    # kernel-argument fetch
+    "-mllvm", "-amdgpu-kernarg-preload-count=6",
     # every uniform-address atomic here is issued by one lane; the atomic
     # optimizer would turn it into a wave-wide scan whose readfirstlane waits
     # for the returned value (and every older load) right after the issue

@@ -7,7 +7,7 @@
 //   2. detect (vanished) : previous list minus the new list -> same outputs,
 //                          and the duplicate check of the new list;
 //   3. layer l = 1..L    : contraction over A_l, Z_l update, delta epilogue,
-//                          A_l -> A_{l+1} propagation;
+//                          A_l -> A_{l+1};
 //   4. the neck          : one upsampling launch per upsampler, when present.
 // Points mode replaces 1 and 2 by the pillar queue update and the pillar
 // feature net (sscater_step_points); a sparse backbone adds the active-set
@@ -45,6 +45,9 @@ struct LayerState {
     void* wpack = nullptr;
     uint32_t* stamp = nullptr;
     int32_t* list = nullptr; // NSHARD segments of Hout*Wout cells
+    // layers after the first of a backbone without active sets (plan.h)
+    uint32_t* bits = nullptr;   // the change list as a bitmap, wpr(Wout) words a row
+    uint16_t* taps = nullptr;   // every list entry's changed taps
     float* wscale = nullptr; // fp32: scale of each output channel's sums
     void* delta = nullptr;   // delta rows of this layer's output, dense by cell (nullptr for the last layer)
     uint16_t* dscale = nullptr;   // fp32: their units' scales
@@ -239,6 +242,50 @@ PropTarget prop_target(sscater* h, int l /* consuming layer, 1..L */, int set) {
     return t;
 }
 
+int words_of(int n) { return (n + 31) / 32; }
+
+// The compaction that builds layer l's list (l >= 2) in the launch of layer
+// l - 1.  A workgroup takes a tile of 128 words (whole rows, or parts of rows
+// longer than 4096 cells), more on grids of over 64 such tiles (up to what its
+// LDS holds): at 432x496 a dozen workgroups that end before the layer's own,
+// and still few on four 1024x1024 images.
+PlanArgs plan_args(sscater* h, int l, int set) {
+    PlanArgs p{};
+    const LayerState& ls = h->layers[l - 1];
+    const LayerState& src = h->layers[l - 2];
+    p.stride = ls.spec.stride;
+    p.Hin = ls.Hin;
+    p.Win = ls.Win;
+    p.wpi = words_of(ls.Win);
+    p.Hout = ls.Hout;
+    p.Wout = ls.Wout;
+    p.wpo = words_of(ls.Wout);
+    const long long words = (long long)h->batch * p.Hout * p.wpo;
+    const int want = (int)std::min<long long>(PLAN_WORDS, std::max<long long>(128, (words + 63) / 64));
+    p.cols = std::min(p.wpo, want);
+    p.chunks = (p.wpo + p.cols - 1) / p.cols;
+    p.rows = std::max(1, std::min(p.Hout, want / p.cols));
+    p.bands = (p.Hout + p.rows - 1) / p.rows;
+    p.tiles = h->batch * p.bands * p.chunks;
+    p.wgs = (p.tiles + 7) / 8 * 8;
+    const int last = p.wpo - (p.chunks - 1) * p.cols;
+    p.dnj[0] = FastDiv((uint32_t)(p.stride * p.cols + 2));
+    p.dnj[1] = FastDiv((uint32_t)(p.stride * last + 2));
+    p.dnx[0] = FastDiv((uint32_t)p.cols);
+    p.dnx[1] = FastDiv((uint32_t)last);
+    p.dwin = FastDiv((uint32_t)p.Win);
+    p.bits_in = src.bits;
+    p.stamp_in = src.stamp;
+    p.bits_out = ls.bits;
+    p.seg = (int)h->cells_of(l);
+    p.list = ls.list;
+    p.taps = ls.taps;
+    p.stamp = ls.stamp;
+    p.count = h->cnt_ptr(set, l);
+    p.pairs = h->pairs_ptr(set, l);
+    return p;
+}
+
 // The layers and the neck of one stride, after A_0 and A_1 are built.
 int run_layers(sscater* h, int set, uint32_t epoch, hipStream_t s) {
     int32_t* cnt = h->set_ptr(set);
@@ -264,9 +311,13 @@ int run_layers(sscater* h, int set, uint32_t epoch, hipStream_t s) {
         a.Wout = ls.Wout;
         a.relu = ls.spec.relu;
         a.epoch = epoch;
-        a.has_next = l < h->L;
-        if (a.has_next) a.next = prop_target(h, l + 1, set);
+        a.dimg = FastDiv((uint32_t)(ls.Hout * ls.Wout));
+        a.drow = FastDiv((uint32_t)ls.Wout);
+        a.taps = h->sparse ? nullptr : ls.taps;
+        if (l < h->L && !h->sparse) a.plan = plan_args(h, l + 1, set);
         if (h->sparse) {
+            a.has_next = l < h->L;
+            if (a.has_next) a.next = prop_target(h, l + 1, set);
             a.memb = ls.memb;
             if (!ls.sub)      // a regular layer passes its membership changes to the next regular layer
                 for (int k = l + 1; k <= h->L; ++k)
@@ -453,6 +504,10 @@ int create_impl(const sscater_grid* grid, int32_t batch, const sscater_layer* la
             SSC_TRY(dev_alloc(h, (void**)&ls.Z, oc * ls.spec.cout * 4));
             SSC_TRY(dev_alloc(h, (void**)&ls.stamp, oc * 4));
             SSC_TRY(dev_alloc(h, (void**)&ls.list, oc * 4 * NSHARD));
+            if (l > 0) {
+                SSC_TRY(dev_alloc(h, (void**)&ls.bits, (size_t)batch * ls.Hout * words_of(ls.Wout) * 4));
+                SSC_TRY(dev_alloc(h, (void**)&ls.taps, oc * 2 * NSHARD));
+            }
             bool feeds_up = false;
             for (int u = 0; u < n_ups; ++u) feeds_up = feeds_up || ups[u].src_layer == l + 1;
             if (l + 1 < n_layers || feeds_up) {

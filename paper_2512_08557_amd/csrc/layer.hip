@@ -11,9 +11,10 @@
 //     launch (scatter rule), so every output cell that receives a scatter
 //     contribution is known up front;
 //   * a workgroup owns TM = 32 consecutive cells of one segment of A_l and up
-//     to 64 output channels.  It looks up the change stamps of the 9 x 32
-//     input cells under the tile's taps and writes the changed cells' indices
-//     to LDS (an unchanged input reads the zero row);
+//     to 64 output channels.  It writes the changed ones of the 9 x 32 input
+//     cells under the tile's taps to LDS, from the list entries' tap bits
+//     (plan.h) or by their change stamps (an unchanged input reads the zero
+//     row);
 //   * the contraction D[cout x 32 cells] += W_t^T[cout x cin] . dY^T over the
 //     9 taps x cin channels is split over the NW wavefronts of the workgroup
 //     by units of 32 channels of one tap: wavefront w takes the units w,
@@ -33,8 +34,9 @@
 //     known; at 256 they stream;
 //   * epilogue in registers: Z_new = Z_old + D; store Z_new; write the next
 //     layer's delta row at the cell;
-//   * the tile's cells are propagated to the next layer's change list (the
-//     structural rule, including stride-2 downsampling).
+//   * the next layer's change list (the structural rule, including stride-2
+//     downsampling) is built by the launch's first workgroups (plan.h), or in
+//     sparse backbones, where it depends on the active sets, by the tiles.
 //
 // MFMA operand layout (v_mfma_f32_16x16x32_f16 / _bf16):
 //   src0 = weights, lane l supplies row cout = l%16, k = 8*(l/16) .. +7;
@@ -66,7 +68,7 @@
 // membership changes to the next block's active-set counts (SPREAD).  Z is
 // updated at every site of the list, active or not, so a site that joins the
 // active set already holds its sum.
-#include "device_common.h"
+#include "plan.h"
 
 #include <algorithm>
 
@@ -106,16 +108,19 @@ struct LayerShape {
     static constexpr int GPC = 1;                        // workgroups per compute unit
 };
 
-// plist, pcount, pcap are a.list, a.count, a.cap passed again as leading
-// scalar arguments: the build preloads them into SGPRs, so the list entry and
-// count loads that open every tile need not wait for the argument fetch.
+// The leading scalar arguments repeat what the struct holds: the build preloads
+// them into SGPRs, so that the loads that open every tile (list entries, tap
+// bits, counts, weights) and the branch to the plan need not wait for the
+// argument fetch, a round trip of its own.
 template <int CIN, int COUT, int S, bool BF16, bool SPARSE, bool SPREAD>
 __global__ __launch_bounds__((64 * LayerShape<CIN, COUT, BF16>::NW)) void layer_kernel(
-    const int32_t* __restrict__ plist, const int32_t* __restrict__ pcount, int pcap, LayerArgs a) {
+    const int32_t* __restrict__ plist, const int32_t* __restrict__ pcount, const uint16_t* __restrict__ ptaps,
+    const char* __restrict__ pweights, int pcap, int pplan, LayerArgs a) {
     using L = LayerShape<CIN, COUT, BF16>;
     constexpr int U = L::U, NB = L::NB, NBN = L::NBN, OB = L::OB, NW = L::NW, CNT = L::CNT, D = L::D, PL = L::PL;
     constexpr int NTH = 64 * NW;
-    constexpr int NE = (9 * TM + NTH - 1) / NTH;         // table entries per thread
+    static_assert(9 * TM <= NTH, "one table entry per thread");
+    static_assert(PLAN_IN * 4 <= NW * 4096 && PLAN_WORDS * (int)sizeof(PlanWord) <= NW * 4096, "plan LDS");
     __shared__ int rowcell[9][TM];                                      // changed input cell, or -1
     __shared__ __attribute__((aligned(16))) uint16_t rowsc[BF16 ? 1 : 9][TM][U];     // its units' 1/s (bf16), or 0
     // the wavefronts' delta units in flight, 4 KB each (one LDS array per slot:
@@ -125,6 +130,13 @@ __global__ __launch_bounds__((64 * LayerShape<CIN, COUT, BF16>::NW)) void layer_
     __shared__ __attribute__((aligned(1024))) char as1[NW * 4096];
     __shared__ __attribute__((aligned(1024))) char as2[D > 2 ? NW * 4096 : 16];
 
+    if constexpr (!SPARSE) {
+        if ((int)blockIdx.x < pplan) {
+            plan_tile<NW>(a.plan, a.epoch, (int)blockIdx.x, reinterpret_cast<uint32_t*>(as0),
+                          reinterpret_cast<PlanWord*>(as1), &rowcell[0][0]);
+            return;
+        }
+    }
     const int tid = (int)threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int cl = lane & 15, g = lane >> 4;
@@ -132,10 +144,11 @@ __global__ __launch_bounds__((64 * LayerShape<CIN, COUT, BF16>::NW)) void layer_
     // workgroup b runs on XCD b % 8: an XCD's workgroups share one group of 64
     // output channels, so its L2 holds that group's weights only; segment and
     // tile follow
-    const int b = (int)blockIdx.x;
+    const int nplan = SPARSE ? 0 : pplan;
+    const int b = (int)blockIdx.x - nplan;
     const int xcd = b & 7, nb = xcd % NBN, idx = b >> 3;
     const int shard = idx & 1;
-    const int GT = (int)gridDim.x / (2 * NBN);
+    const int GT = ((int)gridDim.x - nplan) / (2 * NBN);
     int tile = (idx >> 1) * (8 / NBN) + xcd / NBN;
     const int32_t* seg = plist + (size_t)shard * pcap;
     const int n = pcount[shard * CSTRIDE];
@@ -143,12 +156,14 @@ __global__ __launch_bounds__((64 * LayerShape<CIN, COUT, BF16>::NW)) void layer_
     // the finishing role of this wavefront: cells 16*fm.., channels c0..
     const int fm = w & 1, fb = (w >> 1) * OB;
     const bool fin = w < L::FW;
-    const bool lead = nb == 0 && w < 2;                  // propagates its 16 cells
+    const bool lead = SPARSE && nb == 0 && w < 2;        // propagates its 16 cells
     const int c0 = nb * 64 + fb * 16;
 
-    // table entries of this thread: tap tid / 32 + e * (NTH / 32), row tid % 32
+    // table entry of this thread: tap tid / 32, row tid % 32
     const int tr = tid & 31, tt = tid >> 5;
+    const uint16_t* tseg = ptaps ? ptaps + (size_t)shard * pcap : nullptr;
     int qt = seg[min(tile * TM + tr, pcap - 1)];
+    uint32_t mk = tseg ? tseg[min(tile * TM + tr, pcap - 1)] : 0u;
 
     // copies: lane l takes the 16-byte piece of row 8k + l/8 that belongs in
     // slot l % 8 of it (piece ^ (row / 2) % 8: the 16 rows read together then
@@ -163,7 +178,7 @@ __global__ __launch_bounds__((64 * LayerShape<CIN, COUT, BF16>::NW)) void layer_
     auto slot = [&](int k) -> lds_char* { return (lds_char*)(k == 0 ? as0 : (k == 1 ? as1 : as2)); };
     const char* dbase = static_cast<const char*>(a.delta_in);
     const char* zrow = static_cast<const char*>(a.zero);
-    const char* wbase = static_cast<const char*>(a.wpack) + (size_t)nb * L::NU * L::WU;   // uniform
+    const char* wbase = pweights + (size_t)nb * L::NU * L::WU;   // uniform
     const uint32_t wl16 = (uint32_t)lane * 16u;
     // weights of unit un
     auto load_w = [&](int un, uint4 (&bw)[PL * NB]) __attribute__((always_inline)) {
@@ -194,31 +209,34 @@ __global__ __launch_bounds__((64 * LayerShape<CIN, COUT, BF16>::NW)) void layer_
         const bool vt = t0 + tr < n, vrow = ef < n;
         const int q = qf;                                // a valid cell also past the segment's end
 
-        // the change stamps of this thread's input cells and their scales,
-        // from clamped (always valid) addresses
+        // this thread's input cell, whether it changed, and its units' scales
+        // (loads from clamped, always valid addresses)
         const int q0 = __builtin_amdgcn_readfirstlane(qt);   // row 0, always valid
         const int p = vt ? qt : q0;
-        const int img = p / (a.Hout * a.Wout), pl = p - img * (a.Hout * a.Wout);
-        const int pr = pl / a.Wout, pc = pl - (pl / a.Wout) * a.Wout;
-        int cell[NE];
-        bool ch[NE];
-        uint32_t ev[NE];
-        uint32_t sc[NE][BF16 ? 1 : (U + 1) / 2];
+        int cell = 0;
+        bool ch = vt && tt < 9;
+        uint32_t ev = a.epoch;
+        const int dr = tt / 3 - 1, dc = tt - 3 * (tt / 3) - 1;
+        if (S == 1 && tseg) {
+            ch = ch && ((mk >> tt) & 1u);
+            cell = ch ? p + dr * a.Win + dc : p;
+        } else {
+            const int img = (int)a.dimg((uint32_t)p), pl = p - img * (a.Hout * a.Wout);
+            const int pr = (int)a.drow((uint32_t)pl), pc = pl - pr * a.Wout;
+            const int ir = S * pr + dr, ic = S * pc + dc;
+            ch = ch && ir >= 0 && ir < a.Hin && ic >= 0 && ic < a.Win;
+            if (tseg) ch = ch && ((mk >> tt) & 1u);
+            cell = img * (a.Hin * a.Win) + min(max(ir, 0), a.Hin - 1) * a.Win + min(max(ic, 0), a.Win - 1);
+            if (!tseg) ev = a.stamp_in[cell];
+        }
+        uint32_t sc[BF16 ? 1 : (U + 1) / 2];
+        if constexpr (!BF16) {
+            const uint16_t* sp = a.scale_in + (size_t)cell * U;
+            if constexpr (U == 1) {
+                sc[0] = *sp;
+            } else {
 #pragma unroll
-        for (int k = 0; k < NE; ++k) {
-            const int t = min(tt + k * (NTH / 32), 8);
-            const int ir = S * pr + t / 3 - 1, ic = S * pc + t % 3 - 1;
-            ch[k] = vt && ir >= 0 && ir < a.Hin && ic >= 0 && ic < a.Win;
-            cell[k] = img * (a.Hin * a.Win) + min(max(ir, 0), a.Hin - 1) * a.Win + min(max(ic, 0), a.Win - 1);
-            ev[k] = a.stamp_in[cell[k]];
-            if constexpr (!BF16) {
-                const uint16_t* sp = a.scale_in + (size_t)cell[k] * U;
-                if constexpr (U == 1) {
-                    sc[k][0] = *sp;
-                } else {
-#pragma unroll
-                    for (int i = 0; i < U / 2; ++i) sc[k][i] = reinterpret_cast<const uint32_t*>(sp)[i];
-                }
+                for (int i = 0; i < U / 2; ++i) sc[i] = reinterpret_cast<const uint32_t*>(sp)[i];
             }
         }
         f4v zo[OB], wsc[OB];
@@ -240,24 +258,25 @@ __global__ __launch_bounds__((64 * LayerShape<CIN, COUT, BF16>::NW)) void layer_
                 prev = memb_prev(mw, a.epoch);
             }
         }
-#pragma unroll
-        for (int k = 0; k < NE; ++k) {
-            const int t = tt + k * (NTH / 32);
-            if (t < 9) {
-                ch[k] = ch[k] && ev[k] == a.epoch;
-                rowcell[t][tr] = ch[k] ? cell[k] : -1;
-                if constexpr (!BF16) {
-                    uint16_t* sp = &rowsc[t][tr][0];
+        ch = ch && ev == a.epoch;
+        if (tt < 9) rowcell[tt][tr] = ch ? cell : -1;
+        auto put_scales = [&]() __attribute__((always_inline)) {
+            if constexpr (!BF16) {
+                if (tt < 9) {
+                    uint16_t* sp = &rowsc[tt][tr][0];
                     if constexpr (U == 1) {
-                        *sp = ch[k] ? (uint16_t)sc[k][0] : 0;
+                        *sp = ch ? (uint16_t)sc[0] : 0;
                     } else {
 #pragma unroll
-                        for (int i = 0; i < U / 2; ++i) reinterpret_cast<uint32_t*>(sp)[i] = ch[k] ? sc[k][i] : 0u;
+                        for (int i = 0; i < U / 2; ++i) reinterpret_cast<uint32_t*>(sp)[i] = ch ? sc[i] : 0u;
                     }
                 }
             }
-        }
-        qt = seg[min((tile + GT) * TM + tr, pcap - 1)];  // the next tile's entry
+        };
+        if constexpr (SPARSE) put_scales();              // they came with the stamps
+        // the next tile's entry
+        qt = seg[min((tile + GT) * TM + tr, pcap - 1)];
+        if (tseg) mk = tseg[min((tile + GT) * TM + tr, pcap - 1)];
         lds_barrier();
 
         // delta units of the 32 rows
@@ -272,13 +291,17 @@ __global__ __launch_bounds__((64 * LayerShape<CIN, COUT, BF16>::NW)) void layer_
         };
 #pragma unroll
         for (int i = 0; i < D; ++i) load_a(i, slot(i));
-        // next layer's change list: the footprint stamps go out behind the
-        // first operands; the list positions are taken once those have
-        // arrived, and the counter's round trip overlaps the contraction
-        // sparse, a regular layer followed by another one (SPREAD): the next
-        // regular layer's words of the sites whose activity flips, loaded now
-        // so that only their swaps end the tile
-        if (a.has_next && lead) prop_issue<4, false>(a.next, q, vrow && (now || prev), g, a.epoch, pb);
+        if constexpr (!BF16 && !SPARSE) {                // the scales arrive while the copies are in flight
+            put_scales();
+            lds_barrier();
+        }
+        // sparse: the next layer's footprint stamps go out behind the first
+        // operands, its list positions are taken once those have arrived (the
+        // counter's round trip overlaps the contraction); a regular layer
+        // followed by another one (SPREAD) loads the next regular layer's
+        // words of the sites whose activity flips now, so that only their
+        // swaps end the tile
+        if (lead && a.has_next) prop_issue<4, false>(a.next, q, vrow && (now || prev), g, a.epoch, pb);
         if (SPREAD && lead) memb_issue(a.mnext, q, a.Hout, a.Wout, g == 0 && vrow && now != prev, mbt);
         PropSlots<4> ps;
 
@@ -355,7 +378,7 @@ __global__ __launch_bounds__((64 * LayerShape<CIN, COUT, BF16>::NW)) void layer_
                 load_a(i + D, slot(i % D));
                 if constexpr (!L::STAT) load_w(unit(wt, i + D), bw[i % D]);
             }
-            if (i == 0 && a.has_next && lead) prop_reserve<4>(a.next, a.epoch, shard, pb, ps);
+            if (i == 0 && lead && a.has_next) prop_reserve<4>(a.next, a.epoch, shard, pb, ps);
             // keep the scheduler from hoisting later loads past this unit
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -387,7 +410,7 @@ __global__ __launch_bounds__((64 * LayerShape<CIN, COUT, BF16>::NW)) void layer_
             epilogue_unit<COUT, BF16, OB>(a, q, c0, g, zo, d, vrow && (COUT % 16 == 0 || 4 * g < COUT), now, prev);
         }
         if (SPREAD && lead) memb_finish(a.mnext, q, a.Hout, a.Wout, mbt, now ? 1 : -1, a.epoch);
-        if (a.has_next && lead) prop_write<4>(a.next, shard, pb, ps);
+        if (lead && a.has_next) prop_write<4>(a.next, shard, pb, ps);
         // the next tile's table may be written now (its barrier orders the
         // sums: a wavefront writes red only after the barrier that every
         // finishing wavefront reaches after reading it)
@@ -422,13 +445,15 @@ static hipError_t launch_shape(const LayerArgs& a, const LaunchCtx& c) {
     // one workgroup per compute unit (a longer list loops over its remaining
     // tiles), at most the tiles of a full list
     const long long most = ((long long)a.cap + TM - 1) / TM * 2 * L::NBN;
-    const int grid = (int)std::max(16LL, std::min(256LL * L::GPC, (most + 15) / 16 * 16));
+    const int grid = (int)std::max(16LL, std::min(256LL * L::GPC, (most + 15) / 16 * 16)) + (SPARSE ? 0 : a.plan.wgs);
+    const int plan = SPARSE ? 0 : a.plan.wgs;
+    const char* w = static_cast<const char*>(a.wpack);
     if constexpr (SPARSE)
         if (a.mnext.memb)
-            return launch_kernel(c, layer_kernel<CI, CO, S, BF16, true, true>, dim3(grid), dim3(64 * L::NW), a.list, a.count,
-                                 a.cap, a);
-    return launch_kernel(c, layer_kernel<CI, CO, S, BF16, SPARSE, false>, dim3(grid), dim3(64 * L::NW), a.list, a.count, a.cap,
-                         a);
+            return launch_kernel(c, layer_kernel<CI, CO, S, BF16, true, true>, dim3(grid), dim3(64 * L::NW), a.list,
+                                 a.count, a.taps, w, a.cap, plan, a);
+    return launch_kernel(c, layer_kernel<CI, CO, S, BF16, SPARSE, false>, dim3(grid), dim3(64 * L::NW), a.list, a.count,
+                         a.taps, w, a.cap, plan, a);
 }
 
 hipError_t launch_layer(const LayerArgs& a, int cin, int cout, int stride, bool bf16, bool sparse, const LaunchCtx& c) {

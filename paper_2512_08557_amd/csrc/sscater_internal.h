@@ -45,6 +45,50 @@ struct PropTarget {
                           // XCD x at pairs[(k * PSPREAD + x) * CSTRIDE]
 };
 
+// n / d for 0 <= n < 2^31 as a multiplication: (n * m) >> s with
+// m = ceil(2^s / d), s = 31 + ceil(log2 d).
+struct FastDiv {
+    uint32_t m = 0, s = 0;
+    FastDiv() = default;
+    explicit FastDiv(uint32_t d) {
+        uint32_t l = 0;
+        while ((1ull << l) < d) ++l;
+        s = 31 + l;
+        m = (uint32_t)(((1ull << s) + d - 1) / d);
+    }
+    __host__ __device__ uint32_t operator()(uint32_t n) const { return (uint32_t)(((uint64_t)n * m) >> s); }
+};
+
+// The next layer's change list as a stream compaction (backbones without
+// active sets, whose change sets follow from the layer before by the
+// structural rule alone): A_l as a bitmap (or, for the first layer, by its
+// stamps) -> A_{l+1} as a bitmap, a list with every entry's changed taps,
+// stamps, and the counters.  Workgroups of layer l's own launch, one per
+// tile of the target grid (whole rows, or parts of very long ones).
+struct PlanArgs {
+    int wgs;                  // workgroups (the tiles, up to a multiple of 8; 0: no plan)
+    int tiles;                // images * bands * chunks
+    int bands, rows;          // tiles down an image, target rows of each
+    int chunks, cols;         // tiles across it, target words of each
+    int stride;
+    int Hin, Win, wpi;        // source image and its words of 32 cells per row
+    int Hout, Wout, wpo;      // target image
+    FastDiv dnj[2], dnx[2];   // division by a tile's source and target words per row (full, last chunk)
+    FastDiv dwin;             // division by Win
+    const uint32_t* bits_in;  // [images][Hin][wpi], or nullptr: stamp_in == epoch
+    const uint32_t* stamp_in; // [images][Hin*Win]
+    uint32_t* bits_out;       // [images][Hout][wpo]
+    int seg;                  // capacity of a list segment
+    int32_t* list;            // NSHARD segments
+    uint16_t* taps;           // bit t: the input under tap t changed; same positions
+    uint32_t* stamp;          // [images][Hout*Wout]
+    int32_t* count;           // as PropTarget
+    int32_t* pairs;
+};
+// What a tile may take in LDS: target words, and source words ((2 * rows + 1)
+// * (2 * cols + 2) at stride 2).
+constexpr int PLAN_WORDS = 384, PLAN_IN = 4096;
+
 // Sparse backbones (regular sparse and submanifold convolutions): every
 // layer's output sites carry an active-set word,
 //   bits 0..31  number of active input sites in the site's receptive field
@@ -108,6 +152,10 @@ struct LayerArgs {
     int Hin, Win, Hout, Wout;
     int relu;
     uint32_t epoch;
+    FastDiv dimg, drow;         // division by Hout * Wout, and by Wout
+    const uint16_t* taps;       // every list entry's changed taps (nullptr: by the stamps)
+    PlanArgs plan;              // the next layer's list
+    // sparse backbones: the next layer's list, from this launch's tiles
     int has_next;
     PropTarget next;
     // sparse backbones: this layer's output active-set words, and where a
