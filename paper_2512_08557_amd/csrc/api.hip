@@ -891,25 +891,25 @@ int sscater_reset(sscater_t h, void* stream) {
     hipError_t e = hipStreamSynchronize(s);
     if (e != hipSuccess) return hip_fail(e);
     const size_t cells = h->cells_of(0);
-    e = launch_fill_zero(h->X, round_up(cells * h->row_bytes, 256), s);
-    for (int l = 0; l < h->L && e == hipSuccess; ++l) {
+    FillList f;
+    bool ok = f.add(h->X, round_up(cells * h->row_bytes, 256));
+    for (int l = 0; l < h->L; ++l) {
         const LayerState& ls = h->layers[l];
-        e = launch_fill_zero(ls.Z, round_up(h->cells_of(l + 1) * ls.spec.cout * 4, 256), s);
+        ok = ok && f.add(ls.Z, round_up(h->cells_of(l + 1) * ls.spec.cout * 4, 256));
+        if (h->sparse && !ls.sub) ok = ok && f.add(ls.memb, round_up(h->cells_of(l + 1) * 8, 256));
     }
-    if (e == hipSuccess && h->Zn) e = launch_fill_zero(h->Zn, round_up((size_t)h->Hn * h->Wn * h->Cn * 4, 256), s);
-    if (e == hipSuccess) e = launch_fill_zero(h->counters, round_up((size_t)2 * h->ncnt() * 4, 256), s);
-    if (e == hipSuccess) e = launch_fill_zero(h->cum, round_up((size_t)h->ncnt() * 8, 256), s);
-    for (int l = 0; l < h->L && e == hipSuccess && h->sparse; ++l) {
-        const LayerState& ls = h->layers[l];
-        if (!ls.sub) e = launch_fill_zero(ls.memb, round_up(h->cells_of(l + 1) * 8, 256), s);
-    }
-    if (e == hipSuccess && h->pfn) {
+    if (h->Zn) ok = ok && f.add(h->Zn, round_up((size_t)h->Hn * h->Wn * h->Cn * 4, 256));
+    ok = ok && f.add(h->counters, round_up((size_t)2 * h->ncnt() * 4, 256));
+    ok = ok && f.add(h->cum, round_up((size_t)h->ncnt() * 8, 256));
+    if (h->pfn) {
         const size_t slots = (size_t)h->pfn_spec.window + 1;
-        e = launch_fill_zero(h->head, round_up(cells * 4, 256), s);
-        if (e == hipSuccess) e = launch_fill_zero(h->tail, round_up(cells * 4, 256), s);
-        if (e == hipSuccess) e = launch_fill_zero(h->scnt, round_up(slots * cells * 4, 256), s);
-        if (e == hipSuccess) e = launch_fill_zero(h->tcount, round_up(slots * CSTRIDE * 4, 256), s);
+        ok = ok && f.add(h->head, round_up(cells * 4, 256));
+        ok = ok && f.add(h->tail, round_up(cells * 4, 256));
+        ok = ok && f.add(h->scnt, round_up(slots * cells * 4, 256));
+        ok = ok && f.add(h->tcount, round_up(slots * CSTRIDE * 4, 256));
     }
+    if (!ok) return SSCATER_E_INVALID_ARG;   // unreachable: FILL_MAX holds every buffer of a handle
+    e = launch_fill_zero(f, s);
     if (e != hipSuccess) return hip_fail(e);
     ++h->epoch;   // every stamp becomes stale
     h->prev_count = 0;

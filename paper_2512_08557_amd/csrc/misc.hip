@@ -70,10 +70,24 @@ __global__ __launch_bounds__(256) void read_masked_kernel(const float* __restric
     }
 }
 
-__global__ __launch_bounds__(256) void fill_zero_kernel(uint4* __restrict__ p, long long n16) {
-    for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n16;
-         i += (long long)gridDim.x * blockDim.x)
-        p[i] = make_uint4(0u, 0u, 0u, 0u);
+// Zero fill of several buffers in one launch: a workgroup takes chunks of 64 KB,
+// numbered through all buffers, and finds a chunk's buffer in the table of
+// first chunks (uniform).  A reset clears a dozen or more maps, small and
+// large: one launch each took 2.8 us at the median for 19 of them on the
+// 432x496 backbone (116 MB, 23 us at the copy rate).
+__global__ __launch_bounds__(256) void fill_zero_kernel(FillArgs a) {
+    for (int c = (int)blockIdx.x; c < a.first[a.n]; c += (int)gridDim.x) {
+        int lo = 0, hi = a.n;                            // the last buffer whose first chunk is <= c
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (a.first[mid] <= c) lo = mid;
+            else hi = mid;
+        }
+        const long long n16 = a.n16[lo], at = (long long)(c - a.first[lo]) * FILL_CHUNK;
+        uint4* p = static_cast<uint4*>(a.p[lo]) + at;
+        const int m = (int)min((long long)FILL_CHUNK, n16 - at);
+        for (int i = (int)threadIdx.x; i < m; i += 256) p[i] = make_uint4(0u, 0u, 0u, 0u);
+    }
 }
 
 static unsigned grid_for(long long n) {
@@ -116,11 +130,21 @@ hipError_t launch_read_slice(const float* Z, void* dst, long long cells, int cto
     return hipGetLastError();
 }
 
-// bytes must be a multiple of 16 (all library buffers are padded to 256 B).
-hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s) {
+bool FillList::add(void* p, size_t bytes) {
+    if (!p || bytes < 16) return true;
+    if (args.n == FILL_MAX) return false;
     const long long n16 = (long long)(bytes / 16);
-    if (n16 == 0) return hipSuccess;
-    hipLaunchKernelGGL(fill_zero_kernel, dim3(grid_for(n16)), dim3(256), 0, s, static_cast<uint4*>(p), n16);
+    args.p[args.n] = p;
+    args.n16[args.n] = n16;
+    args.first[args.n + 1] = args.first[args.n] + (int)((n16 + FILL_CHUNK - 1) / FILL_CHUNK);
+    ++args.n;
+    return true;
+}
+
+hipError_t launch_fill_zero(const FillList& f, hipStream_t s) {
+    const int chunks = f.args.first[f.args.n];
+    if (chunks == 0) return hipSuccess;
+    hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)(chunks < 4096 ? chunks : 4096)), dim3(256), 0, s, f.args);
     return hipGetLastError();
 }
 

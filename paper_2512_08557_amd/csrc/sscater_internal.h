@@ -298,7 +298,20 @@ size_t up_wpack_bytes(int cin, int cout, int stride);
 hipError_t launch_pack_weights(const void* w, int cin, int cout, bool bf16, float* fwd, float* inv, void* out);
 hipError_t launch_pack_up_weights(const void* w, int cin, int cout, int stride, bool bf16, float* fwd, float* inv,
                                   void* out);
-hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s);
+// Buffers to clear (bytes a multiple of 16: all library buffers are padded to
+// 256); at most FILL_MAX, enough for every buffer of a handle.
+constexpr int FILL_MAX = 80, FILL_CHUNK = 4096;   // 16-byte values per chunk
+struct FillArgs {
+    int n = 0;
+    int first[FILL_MAX + 1] = {};   // first chunk of every buffer, and the end
+    long long n16[FILL_MAX];
+    void* p[FILL_MAX];
+};
+struct FillList {
+    FillArgs args;
+    bool add(void* p, size_t bytes);   // false: no room
+};
+hipError_t launch_fill_zero(const FillList& f, hipStream_t s);
 hipError_t launch_pillar_update(const PillarArgs& a, int insert_blocks, const LaunchCtx& c);
 hipError_t launch_pfn(const PfnArgs& a, bool bf16, int blocks, const LaunchCtx& c);
 
