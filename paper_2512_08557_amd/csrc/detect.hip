@@ -48,6 +48,9 @@ __device__ __forceinline__ void emit_rows(const DetectArgs& a, int p, int pc, bo
     const int c0 = sub * CL;
     const bool d = act && (tog || nv.x != ov.x || nv.y != ov.y || nv.z != ov.z || nv.w != ov.w);
     const unsigned long long bal = __ballot(d);
+    // most wavefronts of a stride see no change (a sector of 5 to 10 % of the
+    // pillars is refreshed) and have nothing further to do
+    if (bal == 0ull) return;
     const unsigned long long gm = (G == 64 ? ~0ull : ((1ull << G) - 1ull)) << gbase;
     const bool gd = (bal & gm) != 0ull;
     // stamp the first layer's footprint while the rows are written; a
