@@ -10,15 +10,15 @@
 //   * the change list A_l of this layer's OUTPUT grid was built by an earlier
 //     launch (scatter rule), so every output cell that receives a scatter
 //     contribution is known up front;
-//   * a workgroup owns TM = 32 consecutive cells of one segment of A_l and up
-//     to 64 output channels.  It writes the changed ones of the 9 x 32 input
-//     cells under the tile's taps to LDS, from the list entries' tap bits
+//   * a workgroup owns TM = 16 or 32 consecutive cells of one segment of A_l
+//     and up to 64 output channels.  It writes the changed ones of the 9 x TM
+//     input cells under the tile's taps to LDS, from the list entries' tap bits
 //     (plan.h) or by their change stamps (an unchanged input reads the zero
 //     row);
 //   * the contraction D[cout x 32 cells] += W_t^T[cout x cin] . dY^T over the
 //     9 taps x cin channels is split over the NW wavefronts of the workgroup
 //     by units of 32 channels of one tap: wavefront w takes the units w,
-//     w + NW, ... for the whole 32 x 64 tile.  No two wavefronts need the same
+//     w + NW, ... for the whole TM x 64 tile.  No two wavefronts need the same
 //     operand, so there is no barrier between the tile's table and its sums:
 //     each loads its own weights straight into registers (packed in operand
 //     order) and copies its own delta rows global->LDS asynchronously (an
@@ -74,11 +74,11 @@
 
 namespace ssc {
 
-constexpr int TM = 32;   // cells per tile
-
-template <int CIN, int COUT, bool BF16>
+template <int CIN, int COUT, bool BF16, int TM = 32>
 struct LayerShape {
     static constexpr int U = units_of(CIN);              // units of a delta row
+    static constexpr int MH = TM / 16;
+    static constexpr int CPU = TM / 8;                   // copies of a unit (1 KB each)
     static constexpr int ROWB = U * UNIT_BYTES;
     static constexpr int NT = COUT >= 64 ? 64 : (COUT + 15) / 16 * 16;   // output channels per workgroup
     static constexpr int NBN = COUT > 64 ? COUT / 64 : 1;                // workgroups per tile
@@ -90,53 +90,44 @@ struct LayerShape {
     static constexpr int CNT = (NU + NW - 1) / NW;       // units of a wavefront, at most
     static constexpr int FULL = NU / NW;                 // units every wavefront has
     static constexpr bool STAT = U <= (BF16 ? 4 : 2);    // weights stay in registers
-    static constexpr int D = CNT < 3 ? CNT : 3;   // units whose loads are in flight
+    static constexpr int D = CNT < 3 ? CNT : 3;          // units whose loads are in flight
     // vector loads certainly issued after the copies of unit i and before it
     // is awaited: the copies and streamed weights of the next D - 1 units (the
     // weights of the first D units come before all copies; its own weights
     // are not counted, the compiler may place them on either side)
     static constexpr int younger(int i) {
         int n = 0;
-        for (int j = i + 1; j < i + D && j < CNT; ++j) n += 4 + (!STAT && j >= D ? PL * NB : 0);
+        for (int j = i + 1; j < i + D && j < CNT; ++j) n += CPU + (!STAT && j >= D ? PL * NB : 0);
         return n;
     }
-    static constexpr int MAXW = (D - 1) * (4 + PL * NB);
+    static constexpr int MAXW = (D - 1) * (CPU + PL * NB);
     // finishing wavefronts: 16 cells and one unit of output channels each (all
     // the channels of a tile of fewer than 64)
     static constexpr int OB = NB == 4 ? 2 : NB;          // blocks
-    static constexpr int FW = 2 * (NB / OB);
-    static constexpr int GPC = 1;                        // workgroups per compute unit
+    static constexpr int FW = MH * (NB / OB);
+    static constexpr int SLOT = TM * UNIT_BYTES;         // a wavefront's unit in LDS
+    static constexpr int SB = SLOT / 1024;               // blocks of partial sums that fit in it
+    static constexpr int PLAN_LDS = PLAN_IN * 4 + PLAN_WORDS * (int)sizeof(PlanWord);
 };
 
-// The leading scalar arguments repeat what the struct holds: the build preloads
-// them into SGPRs, so that the loads that open every tile (list entries, tap
-// bits, counts, weights) and the branch to the plan need not wait for the
-// argument fetch, a round trip of its own.
-template <int CIN, int COUT, int S, bool BF16, bool SPARSE, bool SPREAD>
-__global__ __launch_bounds__((64 * LayerShape<CIN, COUT, BF16>::NW)) void layer_kernel(
-    const int32_t* __restrict__ plist, const int32_t* __restrict__ pcount, const uint16_t* __restrict__ ptaps,
-    const char* __restrict__ pweights, int pcap, int pplan, LayerArgs a) {
-    using L = LayerShape<CIN, COUT, BF16>;
+// The tiles of TM cells of one workgroup; b: its number among the grid's
+// workgroups that walk tiles, nwg: how many those are.
+template <int CIN, int COUT, int S, bool BF16, bool SPARSE, bool SPREAD, int TM>
+__device__ __forceinline__ void layer_tiles(const int32_t* __restrict__ plist, const uint16_t* __restrict__ ptaps,
+                                            const char* __restrict__ pweights, int pcap, int n0, int n1, int b, int nwg,
+                                            const LayerArgs& a) {
+    using L = LayerShape<CIN, COUT, BF16, TM>;
     constexpr int U = L::U, NB = L::NB, NBN = L::NBN, OB = L::OB, NW = L::NW, CNT = L::CNT, D = L::D, PL = L::PL;
-    constexpr int NTH = 64 * NW;
+    constexpr int NTH = 64 * NW, MH = L::MH, SLOT = L::SLOT, SB = L::SB;
     static_assert(9 * TM <= NTH, "one table entry per thread");
-    static_assert(PLAN_IN * 4 <= NW * 4096 && PLAN_WORDS * (int)sizeof(PlanWord) <= NW * 4096, "plan LDS");
     __shared__ int rowcell[9][TM];                                      // changed input cell, or -1
     __shared__ __attribute__((aligned(16))) uint16_t rowsc[BF16 ? 1 : 9][TM][U];     // its units' 1/s (bf16), or 0
-    // the wavefronts' delta units in flight, 4 KB each (one LDS array per slot:
-    // the compiler then tracks the copies into each slot separately); at the
-    // end slots 0 and 1 take the partial sums of the two cell halves
-    __shared__ __attribute__((aligned(1024))) char as0[NW * 4096];
-    __shared__ __attribute__((aligned(1024))) char as1[NW * 4096];
-    __shared__ __attribute__((aligned(1024))) char as2[D > 2 ? NW * 4096 : 16];
-
-    if constexpr (!SPARSE) {
-        if ((int)blockIdx.x < pplan) {
-            plan_tile<NW>(a.plan, a.epoch, (int)blockIdx.x, reinterpret_cast<uint32_t*>(as0),
-                          reinterpret_cast<PlanWord*>(as1), &rowcell[0][0]);
-            return;
-        }
-    }
+    // the wavefronts' delta units in flight (one LDS array per slot: the
+    // compiler then tracks the copies into each slot separately); at the end
+    // slots 0 and 1 take the partial sums
+    __shared__ __attribute__((aligned(1024))) char as0[NW * SLOT];
+    __shared__ __attribute__((aligned(1024))) char as1[NW * SLOT];
+    __shared__ __attribute__((aligned(1024))) char as2[D > 2 ? NW * SLOT : 16];
     const int tid = (int)threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int cl = lane & 15, g = lane >> 4;
@@ -144,23 +135,21 @@ __global__ __launch_bounds__((64 * LayerShape<CIN, COUT, BF16>::NW)) void layer_
     // workgroup b runs on XCD b % 8: an XCD's workgroups share one group of 64
     // output channels, so its L2 holds that group's weights only; segment and
     // tile follow
-    const int nplan = SPARSE ? 0 : pplan;
-    const int b = (int)blockIdx.x - nplan;
     const int xcd = b & 7, nb = xcd % NBN, idx = b >> 3;
     const int shard = idx & 1;
-    const int GT = ((int)gridDim.x - nplan) / (2 * NBN);
+    const int GT = nwg / (2 * NBN);
     int tile = (idx >> 1) * (8 / NBN) + xcd / NBN;
     const int32_t* seg = plist + (size_t)shard * pcap;
-    const int n = pcount[shard * CSTRIDE];
+    const int n = shard ? n1 : n0;
 
     // the finishing role of this wavefront: cells 16*fm.., channels c0..
-    const int fm = w & 1, fb = (w >> 1) * OB;
+    const int fm = w % MH, fb = w / MH * OB;
     const bool fin = w < L::FW;
-    const bool lead = SPARSE && nb == 0 && w < 2;        // propagates its 16 cells
+    const bool lead = SPARSE && nb == 0 && w < MH;       // propagates its 16 cells
     const int c0 = nb * 64 + fb * 16;
 
-    // table entry of this thread: tap tid / 32, row tid % 32
-    const int tr = tid & 31, tt = tid >> 5;
+    // table entry of this thread
+    const int tr = tid % TM, tt = tid / TM;
     const uint16_t* tseg = ptaps ? ptaps + (size_t)shard * pcap : nullptr;
     int qt = seg[min(tile * TM + tr, pcap - 1)];
     uint32_t mk = tseg ? tseg[min(tile * TM + tr, pcap - 1)] : 0u;
@@ -171,7 +160,7 @@ __global__ __launch_bounds__((64 * LayerShape<CIN, COUT, BF16>::NW)) void layer_
     const int cr = lane >> 3;
     const uint32_t cp0 = (uint32_t)(((lane & 7) ^ (cr >> 1)) * 16), cp1 = cp0 ^ 64u;   // even and odd k
     const int sa = (cl >> 1) & 7;
-    int a_hi = w * 4096 + cl * UNIT_BYTES + ((g ^ sa) << 4), a_lo = a_hi ^ 64;
+    int a_hi = w * SLOT + cl * UNIT_BYTES + ((g ^ sa) << 4), a_lo = a_hi ^ 64;
     // (single values: the compiler's copy tracking follows only a short
     // address chain from the slot's array)
     asm("" : "+v"(a_hi), "+v"(a_lo));
@@ -283,10 +272,10 @@ __global__ __launch_bounds__((64 * LayerShape<CIN, COUT, BF16>::NW)) void layer_
         auto load_a = [&](int i, lds_char* st) __attribute__((always_inline)) {
             const int un = unit(wt, i), t = un / U, u = un - t * U;
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
+            for (int k = 0; k < L::CPU; ++k) {
                 const int rc = rowcell[t][8 * k + cr];
                 const char* src = rc >= 0 ? dbase + (size_t)rc * L::ROWB + u * UNIT_BYTES : zrow;
-                copy16(src + (k & 1 ? cp1 : cp0), st + wt * 4096 + k * 1024);
+                copy16(src + (k & 1 ? cp1 : cp0), st + wt * SLOT + k * 1024);
             }
         };
 #pragma unroll
@@ -305,21 +294,21 @@ __global__ __launch_bounds__((64 * LayerShape<CIN, COUT, BF16>::NW)) void layer_
         if (SPREAD && lead) memb_issue(a.mnext, q, a.Hout, a.Wout, g == 0 && vrow && now != prev, mbt);
         PropSlots<4> ps;
 
-        f4v acc[2][NB];
+        f4v acc[MH][NB];
 #pragma unroll
-        for (int m = 0; m < 2; ++m)
+        for (int m = 0; m < MH; ++m)
 #pragma unroll
             for (int i = 0; i < NB; ++i) acc[m][i] = f4v{0.f, 0.f, 0.f, 0.f};
         auto compute = [&](int i, const lds_char* st, const uint4 (&bv)[PL * NB]) __attribute__((always_inline)) {
             const int un = unit(wt, i), t = un / U, u = un - t * U;
-            uint4 av[4];
+            uint4 av[2 * MH];
 #pragma unroll
-            for (int m = 0; m < 2; ++m) {
+            for (int m = 0; m < MH; ++m) {
                 av[2 * m] = lds16(st + a_hi + m * 2048);
                 av[2 * m + 1] = lds16(st + a_lo + m * 2048);
             }
 #pragma unroll
-            for (int m = 0; m < 2; ++m) {
+            for (int m = 0; m < MH; ++m) {
                 if constexpr (BF16) {
                     const uint4 v = av[2 * m], o = av[2 * m + 1];
                     const uint32_t sg = 0x80008000u;
@@ -384,24 +373,26 @@ __global__ __launch_bounds__((64 * LayerShape<CIN, COUT, BF16>::NW)) void layer_
         }
 
         // partial sums, added in wavefront order by the finishing wavefronts
+        auto red = [&](int ww, int j) __attribute__((always_inline)) {   // block j of wavefront ww
+            return reinterpret_cast<f4v*>((j / SB == 0 ? as0 : as1) + ww * SLOT + (j % SB) * 1024) + lane;
+        };
+        static_assert(MH * NB <= 2 * SB, "partial sums");
 #pragma unroll
-        for (int m = 0; m < 2; ++m) {
-            f4v* red = reinterpret_cast<f4v*>(m == 0 ? as0 : as1) + w * 256 + lane;
+        for (int m = 0; m < MH; ++m)
 #pragma unroll
-            for (int k = 0; k < NB; ++k) red[k * 64] = acc[m][k];
-        }
+            for (int k = 0; k < NB; ++k) *red(w, m * NB + k) = acc[m][k];
         lds_barrier();
         if (fin) {
-            const f4v* red = reinterpret_cast<const f4v*>(fm == 0 ? as0 : as1) + fb * 64 + lane;
             f4v d[OB];
 #pragma unroll
             for (int i = 0; i < OB; ++i) {
-                d[i] = red[i * 64];
+                const int j = fm * NB + fb + i;
+                d[i] = *red(0, j);
 #pragma unroll
                 for (int k = 1; k < NW; ++k) {
-                    const f4v x = red[k * 256 + i * 64];
+                    const f4v x = *red(k, j);
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) d[i][j] += x[j];
+                    for (int e = 0; e < 4; ++e) d[i][e] += x[e];
                 }
                 if constexpr (!BF16)
 #pragma unroll
@@ -421,6 +412,44 @@ __global__ __launch_bounds__((64 * LayerShape<CIN, COUT, BF16>::NW)) void layer_
             }
         }
     }
+}
+
+// The leading scalar arguments repeat what the struct holds: the build preloads
+// them into SGPRs, so that the loads that open every tile (list entries, tap
+// bits, counts, weights) and the branch to the plan need not wait for the
+// argument fetch, a round trip of its own.
+//
+// Tile height: 32 cells, so that a tile's share of the weights is small; up to
+// 64 input channels 16 where the list then still has a workgroup for every
+// tile, on twice the compute units with half the operands and sums each.
+// Measured on a 432x496 stride, 16 against 32 cells: 64->128 stride-2 launch
+// (45 32-cell tiles) 6.3 against 7.7 us, 64->64 (100 to 140 tiles) 7.0 against
+// 8.0 us; on lists of more tiles than workgroups 16 cells lose (four 1024x1024
+// images, 1500 tiles: 45 against 33 us, two workgroups per compute unit).
+template <int CIN, int COUT, int S, bool BF16, bool SPARSE, bool SPREAD>
+__global__ __launch_bounds__((64 * LayerShape<CIN, COUT, BF16>::NW)) void layer_kernel(
+    const int32_t* __restrict__ plist, const int32_t* __restrict__ pcount, const uint16_t* __restrict__ ptaps,
+    const char* __restrict__ pweights, int pcap, int pplan, LayerArgs a) {
+    using L = LayerShape<CIN, COUT, BF16>;
+    if constexpr (!SPARSE) {
+        if ((int)blockIdx.x < pplan) {
+            __shared__ __attribute__((aligned(16))) char planlds[L::PLAN_LDS];
+            __shared__ int plansum[2 * L::NW + 2];
+            plan_tile<L::NW>(a.plan, a.epoch, (int)blockIdx.x, reinterpret_cast<uint32_t*>(planlds),
+                             reinterpret_cast<PlanWord*>(planlds + PLAN_IN * 4), plansum);
+            return;
+        }
+    }
+    const int nplan = SPARSE ? 0 : pplan;
+    const int b = (int)blockIdx.x - nplan, nwg = (int)gridDim.x - nplan;
+    const int n0 = pcount[0], n1 = pcount[CSTRIDE];
+    if constexpr (L::U <= 2) {
+        if (max(n0, n1) <= 16 * (nwg / (2 * L::NBN))) {
+            layer_tiles<CIN, COUT, S, BF16, SPARSE, SPREAD, 16>(plist, ptaps, pweights, pcap, n0, n1, b, nwg, a);
+            return;
+        }
+    }
+    layer_tiles<CIN, COUT, S, BF16, SPARSE, SPREAD, 32>(plist, ptaps, pweights, pcap, n0, n1, b, nwg, a);
 }
 
 // ---------------------------------------------------------------------------
@@ -444,8 +473,8 @@ static hipError_t launch_shape(const LayerArgs& a, const LaunchCtx& c) {
     using L = LayerShape<CI, CO, BF16>;
     // one workgroup per compute unit (a longer list loops over its remaining
     // tiles), at most the tiles of a full list
-    const long long most = ((long long)a.cap + TM - 1) / TM * 2 * L::NBN;
-    const int grid = (int)std::max(16LL, std::min(256LL * L::GPC, (most + 15) / 16 * 16)) + (SPARSE ? 0 : a.plan.wgs);
+    const long long most = ((long long)a.cap + 15) / 16 * 2 * L::NBN;
+    const int grid = (int)std::max(16LL, std::min(256LL, (most + 15) / 16 * 16)) + (SPARSE ? 0 : a.plan.wgs);
     const int plan = SPARSE ? 0 : a.plan.wgs;
     const char* w = static_cast<const char*>(a.wpack);
     if constexpr (SPARSE)
