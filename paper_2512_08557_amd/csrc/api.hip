@@ -100,6 +100,10 @@ struct sscater {
     uint32_t* stamp0 = nullptr;
     void* delta0 = nullptr;        // input delta rows, dense by cell
     uint16_t* dscale0 = nullptr;   // fp32: their units' scales
+    // the first layer's list as a bitmap by cell index, for the second's plan;
+    // alternating between strides: the detection of one clears the other's
+    uint32_t* flat[2] = {nullptr, nullptr};
+    int flat_n = 0;                // 16-byte values of one
     int32_t* prev[2] = {nullptr, nullptr};
     int prev_slot = 0;
     int32_t prev_count = 0;
@@ -239,6 +243,7 @@ PropTarget prop_target(sscater* h, int l /* consuming layer, 1..L */, int set) {
     t.list = ls.list;
     t.count = h->cnt_ptr(set, l);
     t.pairs = h->pairs_ptr(set, l);
+    t.bits = l == 1 && !h->sparse ? h->flat[set] : nullptr;
     return t;
 }
 
@@ -273,9 +278,8 @@ PlanArgs plan_args(sscater* h, int l, int set) {
     p.dnj[1] = FastDiv((uint32_t)(p.stride * last + 2));
     p.dnx[0] = FastDiv((uint32_t)p.cols);
     p.dnx[1] = FastDiv((uint32_t)last);
-    p.dwin = FastDiv((uint32_t)p.Win);
     p.bits_in = src.bits;
-    p.stamp_in = src.stamp;
+    p.flat_in = h->flat[set];
     p.bits_out = ls.bits;
     p.seg = (int)h->cells_of(l);
     p.list = ls.list;
@@ -504,6 +508,10 @@ int create_impl(const sscater_grid* grid, int32_t batch, const sscater_layer* la
             SSC_TRY(dev_alloc(h, (void**)&ls.Z, oc * ls.spec.cout * 4));
             SSC_TRY(dev_alloc(h, (void**)&ls.stamp, oc * 4));
             SSC_TRY(dev_alloc(h, (void**)&ls.list, oc * 4 * NSHARD));
+            if (l == 0 && n_layers > 1) {
+                h->flat_n = (int)((oc / 32 + 2 + 3) / 4);   // one word past the last cell's
+                for (int k = 0; k < 2; ++k) SSC_TRY(dev_alloc(h, (void**)&h->flat[k], (size_t)h->flat_n * 16));
+            }
             if (l > 0) {
                 SSC_TRY(dev_alloc(h, (void**)&ls.bits, (size_t)batch * ls.Hout * words_of(ls.Wout) * 4));
                 SSC_TRY(dev_alloc(h, (void**)&ls.taps, oc * 2 * NSHARD));
@@ -621,6 +629,8 @@ static int step_impl(sscater_t h, const sscater_pillars* pl, void* stream, bool 
     d.scale0 = h->dscale0;
     d.zero_ptr = h->set_ptr(set ^ 1);
     d.zero_n = h->nlines();
+    d.clear = h->sparse ? nullptr : reinterpret_cast<uint4*>(h->flat[set ^ 1]);
+    d.clear_n = h->flat_n;
     d.HW = (int32_t)cells;
     d.epoch = epoch;
     d.err = h->err_dev;
@@ -658,6 +668,7 @@ static int step_impl(sscater_t h, const sscater_pillars* pl, void* stream, bool 
         v.prev_out = nullptr;
         v.zero_ptr = nullptr;
         v.zero_n = 0;
+        v.clear = nullptr;
         e = timed_launch(h, 1, s, [&](const LaunchCtx& c) { return launch_detect_vanished(v, h->row_bytes, h->bf16, c); });
         if (e != hipSuccess) return hip_fail(e);
     }
@@ -775,6 +786,8 @@ int sscater_step_points(sscater_t h, const float* points, int32_t n_points, void
     u.count0 = h->cnt_ptr(set, 0);
     u.zero_ptr = h->set_ptr(set ^ 1);
     u.zero_n = h->nlines();
+    u.clear = reinterpret_cast<uint4*>(h->flat[set ^ 1]);
+    u.clear_n = h->flat_n;
     u.epoch = epoch;
     // the leaving stride touched at most max_new_points cells
     u.n_pop_blocks = std::max(1, std::min(64, (p.max_new_points + 255) / 256));
@@ -901,6 +914,7 @@ int sscater_reset(sscater_t h, void* stream) {
     if (h->Zn) ok = ok && f.add(h->Zn, round_up((size_t)h->Hn * h->Wn * h->Cn * 4, 256));
     ok = ok && f.add(h->counters, round_up((size_t)2 * h->ncnt() * 4, 256));
     ok = ok && f.add(h->cum, round_up((size_t)h->ncnt() * 8, 256));
+    for (int k = 0; k < 2; ++k) ok = ok && f.add(h->flat[k], (size_t)h->flat_n * 16);
     if (h->pfn) {
         const size_t slots = (size_t)h->pfn_spec.window + 1;
         ok = ok && f.add(h->head, round_up(cells * 4, 256));

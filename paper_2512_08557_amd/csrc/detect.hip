@@ -180,6 +180,7 @@ __global__ __launch_bounds__(256) void detect_kernel(DetectArgs a) {
 
     if (!VANISH && a.zero_ptr && blockIdx.x == 0)
         for (int i = threadIdx.x; i < a.zero_n; i += blockDim.x) a.zero_ptr[(size_t)i * CSTRIDE] = 0;
+    if (!VANISH && a.clear) clear_grid(a.clear, a.clear_n);
 
     const int wave = (int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
     const int nwaves = (int)((gridDim.x * blockDim.x) >> 6);
@@ -282,6 +283,7 @@ __global__ __launch_bounds__(256) void detect_sorted_kernel(DetectArgs a) {
 
     if (a.zero_ptr && blockIdx.x == 0)
         for (int i = threadIdx.x; i < a.zero_n; i += blockDim.x) a.zero_ptr[(size_t)i * CSTRIDE] = 0;
+    if (a.clear) clear_grid(a.clear, a.clear_n);
 
     for (int k = (int)blockIdx.x; k < nchunk; k += (int)gridDim.x) {
         if (w < 3) {

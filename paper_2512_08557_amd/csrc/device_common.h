@@ -92,7 +92,10 @@ __device__ __forceinline__ void prop_finish(const PropTarget& t, uint32_t epoch,
     int32_t* seg = t.list + (size_t)shard * t.seg;
 #pragma unroll
     for (int it = 0; it < IT; ++it) {
-        if (own[it]) seg[base + (int)__popcll(ob[it] & lt)] = pb.q[it];
+        if (own[it]) {
+            seg[base + (int)__popcll(ob[it] & lt)] = pb.q[it];
+            if (t.bits) atomicOr(&t.bits[pb.q[it] >> 5], 1u << (pb.q[it] & 31));
+        }
         base += (int)__popcll(ob[it]);
     }
 }
@@ -256,7 +259,10 @@ __device__ __forceinline__ void prop_write(const PropTarget& t, int shard, const
     int32_t* seg = t.list + (size_t)shard * t.seg;
 #pragma unroll
     for (int it = 0; it < IT; ++it) {
-        if (ps.own[it]) seg[base + (int)__popcll(ps.ob[it] & lt)] = pb.q[it];
+        if (ps.own[it]) {
+            seg[base + (int)__popcll(ps.ob[it] & lt)] = pb.q[it];
+            if (t.bits) atomicOr(&t.bits[pb.q[it] >> 5], 1u << (pb.q[it] & 31));
+        }
         base += (int)__popcll(ps.ob[it]);
     }
 }
@@ -266,6 +272,12 @@ __device__ __forceinline__ uint32_t f32_to_bf16_bits(float f) {
     uint32_t u = __float_as_uint(f);
     u += 0x7FFFu + ((u >> 16) & 1u);
     return u >> 16;
+}
+
+// Clears n 16-byte values, spread over the grid.
+__device__ __forceinline__ void clear_grid(uint4* p, int n) {
+    for (int i = (int)(blockIdx.x * blockDim.x + threadIdx.x); i < n; i += (int)(gridDim.x * blockDim.x))
+        p[i] = make_uint4(0u, 0u, 0u, 0u);
 }
 
 // ---- delta rows ----

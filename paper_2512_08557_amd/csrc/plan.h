@@ -77,30 +77,16 @@ __device__ __forceinline__ void plan_tile(const PlanArgs& t, uint32_t epoch, int
             lin[k] = in ? v : 0u;
         }
     } else {
-        // by the stamps: 16-byte loads over the rows' cells (the tile takes
-        // whole rows: a grid whose rows are chunked is read once per chunk)
-        for (int k = tid; k < nwi; k += NTH) lin[k] = 0u;
-        __syncthreads();
-        const int lo = max(i0, 0), hi = min(i0 + ni, t.Hin);
-        const size_t base = (size_t)img * t.Hin * t.Win;
-        const size_t a = base + (size_t)lo * t.Win, e = base + (size_t)hi * t.Win;
-        const uint4* st4 = reinterpret_cast<const uint4*>(t.stamp_in);   // 16-byte aligned, padded to 256 bytes
-        for (size_t q = a / 4 + tid; q * 4 < e; q += 8 * NTH) {
-            uint4 v[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] = st4[min(q + j * NTH, (e - 1) / 4)];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const uint32_t s[4] = {v[j].x, v[j].y, v[j].z, v[j].w};
-                const size_t c0 = (q + j * NTH) * 4;
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    if (s[k] == epoch && c0 + k >= a && c0 + k < e) {
-                        const int p = (int)(c0 + k - base), r = (int)t.dwin((uint32_t)p), c = p - r * t.Win;
-                        const int x = (c >> 5) - j0;
-                        if (x >= 0 && x < nj) atomicOr(&lin[(r - i0) * nj + x], 1u << (c & 31));
-                    }
-            }
+        // by cell index: a row's word straddles two
+        for (int k = tid; k < nwi; k += NTH) {
+            const int r = (int)t.dnj[nx == t.cols ? 0 : 1]((uint32_t)k);
+            const int i = i0 + r, j = j0 + k - r * nj;
+            const bool in = i >= 0 && i < t.Hin && j >= 0 && j < t.wpi;
+            const int at = (img * t.Hin + min(max(i, 0), t.Hin - 1)) * t.Win + 32 * min(max(j, 0), t.wpi - 1);
+            const uint64_t v = (uint64_t)t.flat_in[at >> 5] | ((uint64_t)t.flat_in[(at >> 5) + 1] << 32);
+            const int left = t.Win - 32 * j;
+            const uint32_t keep = left >= 32 ? ~0u : (1u << (left & 31)) - 1u;
+            lin[k] = in ? (uint32_t)(v >> (at & 31)) & keep : 0u;
         }
     }
     __syncthreads();

@@ -43,6 +43,7 @@ struct PropTarget {
     int32_t* count;       // segment lengths, segment k at count[k * CSTRIDE]
     int32_t* pairs;       // (input, output) pairs of the consuming layer: segment k,
                           // XCD x at pairs[(k * PSPREAD + x) * CSTRIDE]
+    uint32_t* bits;       // the listed cells as a bitmap by cell index (nullptr: not wanted)
 };
 
 // n / d for 0 <= n < 2^31 as a multiplication: (n * m) >> s with
@@ -61,8 +62,7 @@ struct FastDiv {
 
 // The next layer's change list as a stream compaction (backbones without
 // active sets, whose change sets follow from the layer before by the
-// structural rule alone): A_l as a bitmap (or, for the first layer, by its
-// stamps) -> A_{l+1} as a bitmap, a list with every entry's changed taps,
+// structural rule alone): A_l as a bitmap -> A_{l+1} as a bitmap, a list with every entry's changed taps,
 // stamps, and the counters.  Workgroups of layer l's own launch, one per
 // tile of the target grid (whole rows, or parts of very long ones).
 struct PlanArgs {
@@ -74,9 +74,8 @@ struct PlanArgs {
     int Hin, Win, wpi;        // source image and its words of 32 cells per row
     int Hout, Wout, wpo;      // target image
     FastDiv dnj[2], dnx[2];   // division by a tile's source and target words per row (full, last chunk)
-    FastDiv dwin;             // division by Win
-    const uint32_t* bits_in;  // [images][Hin][wpi], or nullptr: stamp_in == epoch
-    const uint32_t* stamp_in; // [images][Hin*Win]
+    const uint32_t* bits_in;  // [images][Hin][wpi]
+    const uint32_t* flat_in;  // or, for the first layer, by cell index (one word more than the cells take)
     uint32_t* bits_out;       // [images][Hout][wpo]
     int seg;                  // capacity of a list segment
     int32_t* list;            // NSHARD segments
@@ -125,6 +124,8 @@ struct DetectArgs {
     uint16_t* scale0;     // fp32: their units' scales, dense by cell [H0*W0][units]
     int32_t* zero_ptr;    // counters to clear for the next stride (may be nullptr)
     int32_t zero_n;       // their lines (word 0 of each CSTRIDE line is the counter)
+    uint4* clear;         // the next stride's bitmap of the first layer's list, cleared here (may be nullptr)
+    int32_t clear_n;      // 16-byte values
     int32_t HW;
     uint32_t epoch;
     int32_t* err;         // sticky error flags (host-visible memory)
@@ -211,6 +212,8 @@ struct PillarArgs {
     int32_t* count0;            // its counters, segment k at [k * CSTRIDE]
     int32_t* zero_ptr;          // counter set of the next stride, cleared here
     int zero_n;                 // its lines
+    uint4* clear;               // the next stride's bitmap of the first layer's list, cleared here (may be nullptr)
+    int clear_n;                // 16-byte values
     uint32_t epoch;
     int n_pop_blocks;           // workgroups [0, n_pop_blocks) remove, the others insert
 };
