@@ -878,12 +878,14 @@ int sscater_read(sscater_t h, int32_t layer, void* dst, size_t dst_bytes, void* 
     if (layer == h->L + 1) {   // the neck map, each upsampler's phi over its channels
         const long long cells = (long long)h->Hn * h->Wn;
         if (dst_bytes < (size_t)cells * h->Cn * esz) return SSCATER_E_INVALID_ARG;
+        uint64_t relu_bits = 0;   // upsamplers have 16 to 128 channels, a multiple of 16
         for (int u = 0; u < h->n_ups; ++u) {
             const UpState& us = h->ups[u];
-            hipError_t e = launch_read_slice(h->Zn, dst, cells, h->Cn, us.coff, us.spec.cout, us.spec.relu, h->bf16, s);
-            if (e != hipSuccess) return hip_fail(e);
+            if (us.spec.relu)
+                for (int c = us.coff; c < us.coff + us.spec.cout; c += 16) relu_bits |= 1ull << (c / 16);
         }
-        return SSCATER_OK;
+        hipError_t e = launch_read_mixed(h->Zn, dst, cells, h->Cn, relu_bits, h->bf16, s);
+        return e == hipSuccess ? SSCATER_OK : hip_fail(e);
     }
     const LayerState& ls = h->layers[layer - 1];
     const long long n = (long long)h->cells_of(layer) * ls.spec.cout;

@@ -286,10 +286,10 @@ hipError_t launch_read(const float* Z, void* dst, long long n, int relu, bool bf
 // phi(Z) with the sites outside the active set (sparse backbones) zeroed.
 hipError_t launch_read_masked(const float* Z, void* dst, long long cells, int cout, const uint64_t* memb, int relu,
                               bool bf16, hipStream_t s);
-// phi of channels [coff, coff + cout) of a [cells][ctot] map into the same
-// channels of a [cells][ctot] destination.
-hipError_t launch_read_slice(const float* Z, void* dst, long long cells, int ctot, int coff, int cout, int relu,
-                             bool bf16, hipStream_t s);
+// phi of a [cells][ctot] map, with ReLU on the groups of 16 channels whose bit
+// is set.
+hipError_t launch_read_mixed(const float* Z, void* dst, long long cells, int ctot, uint64_t relu_bits, bool bf16,
+                             hipStream_t s);
 bool upsample_supported(int cin, int cout, int stride);
 hipError_t launch_upsample(const UpArgs& a, int cin, int cout, int stride, bool bf16, const LaunchCtx& c);
 // Weights in the layouts the kernels read (see layer.hip), packed on the device
