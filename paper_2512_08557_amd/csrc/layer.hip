@@ -29,9 +29,9 @@
 //     is exactly the sum the scatter of Eq. 2 adds into that cell, so the
 //     result is deterministic (it does not depend on the other cells of the
 //     tile) and each Z row is read and written once per stride;
-//   * up to 128 input channels (STAT) a wavefront's weights stay in its
-//     registers for all the tiles of its workgroup, loaded before the list is
-//     known; at 256 they stream;
+//   * up to 64 input channels (128 in bf16; STAT) a wavefront's weights stay in
+//     its registers for all the tiles of its workgroup, loaded before the list
+//     is known; wider layers stream them;
 //   * epilogue in registers: Z_new = Z_old + D; store Z_new; write the next
 //     layer's delta row at the cell;
 //   * the next layer's change list (the structural rule, including stride-2
@@ -54,10 +54,10 @@
 // clock and compute unit (a 32 x 64 tile of a 256-channel layer takes 864 KB,
 // 5.8 us).  Measured per launch against what ran before (fp32 matrix
 // instructions; the wide layers as a contraction plus a tap sum), 432x496
-// backbone, ~4300 / 2300 / 1000 output cells: 64->64 11.5 -> 9.3 us, 128->128
-// 9.9 + 5.8 -> 10.7, 256->256 14.5 + 5.6 -> 13.9; bf16 8.8 -> 7.5, 5.3 + 5.4
-// -> 8.7, 6.6 + 5.0 -> 10.4; the first window (all cells) 48 -> 27, 38 + 20 ->
-// 30.5, 40 + 10 -> 27.7; four 1024x1024 images 64->64 70.7 -> 37.7.  With the
+// backbone, ~4300 / 2300 / 1000 output cells: 64->64 11.5 -> 6.8 us, 128->128
+// 9.9 + 5.8 -> 10.0, 256->256 14.5 + 5.6 -> 13.9; the first window (all cells)
+// 48 -> 27, 38 + 20 -> 30.5, 40 + 10 -> 27.7; four 1024x1024 images 64->64
+// 70.7 -> 37.7.  With the
 // same tile as a workgroup-wide ring of LDS stages instead (both operands
 // shared, a barrier per stage) a 256->256 launch took 21.9 us, and with the
 // delta rows loaded in operand order straight into registers 17.6.
