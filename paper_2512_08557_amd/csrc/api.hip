@@ -137,6 +137,8 @@ struct sscater {
     long long steps = 0;
     int32_t last_pillars = 0;
     std::vector<void*> allocs;
+    char* chunk = nullptr;   // small buffers share allocations (dev_alloc)
+    size_t chunk_left = 0;
     // per-kernel event timing (metrics extension)
     struct ProfRec {
         int slot;
@@ -176,13 +178,32 @@ struct DeviceGuard {
     }
 };
 
+// A device allocation and its clearing take a few hundred us each, whatever
+// their size: buffers of at most SMALL bytes (counters, scales, bitmaps, most
+// weights and stamps) are cut from chunks that are allocated and cleared as one.
 int dev_alloc(sscater* h, void** p, size_t bytes) {
+    constexpr size_t SMALL = (size_t)1 << 20, CHUNK = (size_t)4 << 20;
+    *p = nullptr;
     bytes = round_up(bytes < 256 ? 256 : bytes, 256);
-    hipError_t e = hipMalloc(p, bytes);
-    if (e != hipSuccess) { *p = nullptr; return hip_fail(e); }
-    h->allocs.push_back(*p);
-    e = hipMemset(*p, 0, bytes);
+    if (bytes <= h->chunk_left) {
+        *p = h->chunk;
+        h->chunk += bytes;
+        h->chunk_left -= bytes;
+        return SSCATER_OK;
+    }
+    const bool small = bytes <= SMALL;
+    const size_t n = small ? CHUNK : bytes;
+    void* d = nullptr;
+    hipError_t e = hipMalloc(&d, n);
     if (e != hipSuccess) return hip_fail(e);
+    h->allocs.push_back(d);
+    e = hipMemset(d, 0, n);
+    if (e != hipSuccess) return hip_fail(e);
+    *p = d;
+    if (small) {
+        h->chunk = (char*)d + bytes;
+        h->chunk_left = n - bytes;
+    }
     return SSCATER_OK;
 }
 
