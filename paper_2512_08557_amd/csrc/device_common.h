@@ -479,6 +479,11 @@ __device__ __forceinline__ uint4 lds16(const lds_char* p) {
     return make_uint4(v.x, v.y, v.z, v.w);
 }
 
+// The value is needed here: nothing that makes it may be moved past this point.
+__device__ __forceinline__ void pin(uint4& v) {
+    asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w));
+}
+
 __device__ __forceinline__ void flag_error(int32_t* err, int bit) {
     *(volatile int32_t*)err = bit;
 }

@@ -92,12 +92,14 @@ struct LayerShape {
     static constexpr bool STAT = U <= (BF16 ? 4 : 2);    // weights stay in registers
     static constexpr int D = CNT < 3 ? CNT : 3;          // units whose loads are in flight
     // vector loads certainly issued after the copies of unit i and before it
-    // is awaited: the copies and streamed weights of the next D - 1 units (the
-    // weights of the first D units come before all copies; its own weights
-    // are not counted, the compiler may place them on either side)
+    // is awaited: the copies of the next D - 1 units and the streamed weights
+    // of those of them that every wavefront has (the weights of the first D
+    // units come before all copies; a unit's own weights and those of a unit
+    // that only some wavefronts compute are not counted, the compiler may place
+    // them on either side of the wait).  A smaller count waits for more.
     static constexpr int younger(int i) {
         int n = 0;
-        for (int j = i + 1; j < i + D && j < CNT; ++j) n += CPU + (!STAT && j >= D ? PL * NB : 0);
+        for (int j = i + 1; j < i + D && j < CNT; ++j) n += CPU + (!STAT && j >= D && j < FULL ? PL * NB : 0);
         return n;
     }
     static constexpr int MAXW = (D - 1) * (CPU + PL * NB);
@@ -358,9 +360,18 @@ __device__ __forceinline__ void layer_tiles(const int32_t* __restrict__ plist, c
         for (int i = 0; i < CNT; ++i) {
             // this wavefront's copies of the unit have landed: everything but
             // what was issued after them (the younger units' copies and
-            // weights; more than that in flight only waits for more)
+            // weights; more than that in flight only waits for more).  What
+            // is read below rests on this count, whatever waits the compiler
+            // adds for the LDS reads
             wait_vm_n<L::MAXW>(L::younger(i));
             asm volatile("" ::: "memory");
+            if constexpr (!L::STAT)
+                if (i >= L::FULL) {
+                    // a use outside the branch: the loads of a unit that only
+                    // some wavefronts compute stay where they were issued
+#pragma unroll
+                    for (int k = 0; k < PL * NB; ++k) pin(bw[i % D][k]);
+                }
             if (i < L::FULL || wt + NW * i < L::NU) compute(i, slot(i % D), bw[L::STAT ? i : i % D]);
             if (i + D < CNT) {
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the slot has been read
@@ -455,11 +466,14 @@ __global__ __launch_bounds__((64 * LayerShape<CIN, COUT, BF16>::NW)) void layer_
 // ---------------------------------------------------------------------------
 // instantiation table
 // ---------------------------------------------------------------------------
+// (a build may give a shorter table of its own)
+#ifndef SSC_ALL_SHAPES
 #define SSC_CH_LIST(X, CIN, S) X(CIN, 8, S) X(CIN, 16, S) X(CIN, 32, S) X(CIN, 64, S) X(CIN, 128, S) X(CIN, 256, S)
 #define SSC_ALL_SHAPES(X)                                                                            \
     SSC_CH_LIST(X, 16, 1) SSC_CH_LIST(X, 32, 1) SSC_CH_LIST(X, 64, 1) SSC_CH_LIST(X, 128, 1)         \
     SSC_CH_LIST(X, 256, 1) SSC_CH_LIST(X, 16, 2) SSC_CH_LIST(X, 32, 2) SSC_CH_LIST(X, 64, 2)         \
     SSC_CH_LIST(X, 128, 2) SSC_CH_LIST(X, 256, 2)
+#endif
 
 bool layer_supported(int cin, int cout, int stride, bool /*bf16*/) {
 #define SSC_SUP(CI, CO, S) if (cin == CI && cout == CO && stride == S) return true;

@@ -1,0 +1,58 @@
+"""The layer kernel's copy pipeline as compiled: a wavefront waits for its
+asynchronous copies by counting the vector loads issued after them, so the
+loads have to stay where the source issues them."""
+import os
+import re
+import subprocess
+
+import pytest
+
+from paper_2512_08557_amd import build as B
+
+
+def _assembly(tmp_path, shapes):
+    src = os.path.join(B.CSRC, "layer.hip")
+    out = str(tmp_path / "layer.s")
+    table = "-DSSC_ALL_SHAPES(X)=" + " ".join(f"X({a},{b},{s})" for a, b, s in shapes)
+    r = subprocess.run([B.HIPCC, *B.COMMON, table, "--cuda-device-only", "-S", src, "-o", out], capture_output=True,
+                       text=True)
+    assert r.returncode == 0, r.stderr
+    with open(out) as f:
+        return f.read()
+
+
+def _kernels(text):
+    for m in re.finditer(r"^(_ZN3ssc12layer_kernel\w+):.*?^\s+s_endpgm", text, re.S | re.M):
+        yield m.group(1), m.group(0)
+
+
+def _blocks(body):
+    """Basic blocks: split at labels and after branches."""
+    cur = []
+    for line in body.splitlines():
+        ins = line.strip()
+        if re.match(r"^\.LBB\w+:", ins):
+            yield cur
+            cur = []
+        elif re.match(r"^[a-z]", ins):
+            cur.append(ins)
+            if ins.startswith(("s_cbranch", "s_branch", "s_setpc")):
+                yield cur
+                cur = []
+    yield cur
+
+
+@pytest.mark.skipif(not os.path.exists(B.HIPCC), reason="needs the HIP compiler")
+def test_weights_are_loaded_ahead_of_a_conditional_unit(tmp_path):
+    """128 input channels: 36 units over 8 wavefronts, so four of them have one
+    unit more, in a branch.  Its weights are issued with the copies of their
+    unit, not inside the branch behind the last wait."""
+    n = 0
+    for name, body in _kernels(_assembly(tmp_path, [(128, 8, 1), (128, 32, 1), (128, 128, 1), (128, 64, 2)])):
+        n += 1
+        for blk in _blocks(body):
+            has = {k: any(i.startswith(k) for i in blk)
+                   for k in ("ds_read_b128", "v_mfma", "global_load_dwordx4", "global_load_lds")}
+            if has["ds_read_b128"] and has["v_mfma"] and has["global_load_dwordx4"]:
+                assert has["global_load_lds"], f"{name}: weights loaded where they are used"
+    assert n == 24
