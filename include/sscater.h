@@ -31,9 +31,9 @@
  *   - each layer: 3x3 kernel, zero padding 1, stride 1 or 2, output extent
  *     (n - 1)/stride + 1 per axis; weights OIHW; no bias; optional ReLU.
  *   - dtype SSCATER_F32: fp32 features, weights, maps and accumulation; a
- *     product is formed from 2 x 11-bit halves of either factor (each factor
- *     to 2^-23 of itself or better, under a common power-of-two scale of 32
- *     channels).
+ *     product is formed from three bf16 parts of either factor, which hold all
+ *     of its 24 bits (down to 2^-133): six of the nine partial products, the
+ *     others being at most 2^-24 of the whole.
  *     dtype SSCATER_BF16: bf16 features, weights and layer outputs (round to
  *     nearest even), fp32 accumulation and fp32 pre-activation maps.
  *   - all device pointers are HIP device memory of the calling process.

@@ -48,9 +48,7 @@ struct LayerState {
     // layers after the first of a backbone without active sets (plan.h)
     uint32_t* bits = nullptr;   // the change list as a bitmap, wpr(Wout) words a row
     uint16_t* taps = nullptr;   // every list entry's changed taps
-    float* wscale = nullptr; // fp32: scale of each output channel's sums
     void* delta = nullptr;   // delta rows of this layer's output, dense by cell (nullptr for the last layer)
-    uint16_t* dscale = nullptr;   // fp32: their units' scales
     // sparse backbones: the output active-set words (owned by a regular
     // layer, shared with the submanifold layers of its block)
     uint64_t* memb = nullptr;
@@ -64,7 +62,6 @@ struct UpState {
     int Hs = 0, Ws = 0;      // source grid
     int coff = 0;            // first channel in the neck map
     void* wpack = nullptr;
-    float* wscale = nullptr;
 };
 
 thread_local char g_hip_err[256] = "no HIP error";
@@ -99,7 +96,6 @@ struct sscater {
     uint64_t* pres = nullptr;
     uint32_t* stamp0 = nullptr;
     void* delta0 = nullptr;        // input delta rows, dense by cell
-    uint16_t* dscale0 = nullptr;   // fp32: their units' scales
     // the first layer's list as a bitmap by cell index, for the second's plan;
     // alternating between strides: the detection of one clears the other's
     uint32_t* flat[2] = {nullptr, nullptr};
@@ -179,7 +175,7 @@ struct DeviceGuard {
 };
 
 // A device allocation and its clearing take a few hundred us each, whatever
-// their size: buffers of at most SMALL bytes (counters, scales, bitmaps, most
+// their size: buffers of at most SMALL bytes (counters, bitmaps, most
 // weights and stamps) are cut from chunks that are allocated and cleared as one.
 int dev_alloc(sscater* h, void** p, size_t bytes) {
     constexpr size_t SMALL = (size_t)1 << 20, CHUNK = (size_t)4 << 20;
@@ -323,13 +319,10 @@ int run_layers(sscater* h, int set, uint32_t epoch, hipStream_t s) {
         a.cap = (int)h->cells_of(l);
         a.stamp_in = l == 1 ? h->stamp0 : h->layers[l - 2].stamp;
         a.delta_in = l == 1 ? h->delta0 : h->layers[l - 2].delta;
-        a.scale_in = l == 1 ? h->dscale0 : h->layers[l - 2].dscale;
         a.zero = h->zero;
         a.wpack = ls.wpack;
-        a.wscale = ls.wscale;
         a.Z = ls.Z;
         a.delta_out = ls.delta;   // allocated when a later layer or an upsampler reads it
-        a.scale_out = ls.dscale;
         a.Hin = ls.Hin;
         a.Win = ls.Win;
         a.Hout = ls.Hout;
@@ -372,9 +365,7 @@ int run_layers(sscater* h, int set, uint32_t epoch, hipStream_t s) {
         a.count = h->cnt_ptr(set, us.spec.src_layer);
         a.cap = src.Hout * src.Wout;
         a.delta_src = src.delta;
-        a.scale_src = src.dscale;
         a.wpack = us.wpack;
-        a.wscale = us.wscale;
         a.Z = h->Zn;
         a.ctot = h->Cn;
         a.coff = us.coff;
@@ -485,8 +476,8 @@ int create_impl(const sscater_grid* grid, int32_t batch, const sscater_layer* la
     int rc = SSCATER_OK;
     const size_t cells = (size_t)cells0;
     const size_t esz = bf16 ? 2 : 4;
-    // the weights as the caller holds them, one layer at a time, and their
-    // channels' scales, for the packing kernels (freed below)
+    // the weights as the caller holds them, one layer at a time, for the
+    // packing kernels (freed below)
     size_t raw_bytes = 0;
     for (int l = 0; l < n_layers; ++l)
         raw_bytes = std::max(raw_bytes, (size_t)9 * layers[l].cin * layers[l].cout * esz);
@@ -494,13 +485,11 @@ int create_impl(const sscater_grid* grid, int32_t batch, const sscater_layer* la
         raw_bytes = std::max(raw_bytes, (size_t)layers[ups[u].src_layer - 1].cout * ups[u].cout * ups[u].stride *
                                             ups[u].stride * esz);
     void* raw = nullptr;
-    float* fwd = nullptr;
-    he = hipMalloc(&raw, raw_bytes + 256 * sizeof(float));
+    he = hipMalloc(&raw, raw_bytes);
     if (he != hipSuccess) {
         delete h;
         return hip_fail(he);
     }
-    fwd = reinterpret_cast<float*>(static_cast<char*>(raw) + raw_bytes);
 #define SSC_TRY(expr)                 \
     do {                              \
         rc = (expr);                  \
@@ -510,7 +499,6 @@ int create_impl(const sscater_grid* grid, int32_t batch, const sscater_layer* la
     SSC_TRY(dev_alloc(h, (void**)&h->pres, cells * 8));
     SSC_TRY(dev_alloc(h, (void**)&h->stamp0, cells * 4));
     SSC_TRY(dev_alloc(h, &h->delta0, cells * delta_row_bytes(grid->C0)));
-    if (!bf16) SSC_TRY(dev_alloc(h, (void**)&h->dscale0, cells * units_of(grid->C0) * 2));
     SSC_TRY(dev_alloc(h, (void**)&h->prev[0], (size_t)grid->max_pillars * 4));
     SSC_TRY(dev_alloc(h, (void**)&h->prev[1], (size_t)grid->max_pillars * 4));
     SSC_TRY(dev_alloc(h, (void**)&h->counters, (size_t)2 * h->ncnt() * 4));
@@ -539,15 +527,11 @@ int create_impl(const sscater_grid* grid, int32_t batch, const sscater_layer* la
             }
             bool feeds_up = false;
             for (int u = 0; u < n_ups; ++u) feeds_up = feeds_up || ups[u].src_layer == l + 1;
-            if (l + 1 < n_layers || feeds_up) {
-                SSC_TRY(dev_alloc(h, &ls.delta, oc * delta_row_bytes(ls.spec.cout)));
-                if (!bf16) SSC_TRY(dev_alloc(h, (void**)&ls.dscale, oc * units_of(ls.spec.cout) * 2));
-            }
-            zero_bytes = std::max(zero_bytes, (size_t)delta_row_bytes(ls.spec.cin));
+            if (l + 1 < n_layers || feeds_up) SSC_TRY(dev_alloc(h, &ls.delta, oc * delta_row_bytes(ls.spec.cout)));
+            zero_bytes = std::max(zero_bytes, (size_t)std::max(UNIT_BYTES, delta_row_bytes(ls.spec.cin)));
             SSC_TRY(dev_alloc(h, &ls.wpack, wpack_bytes(ls.spec.cin, ls.spec.cout, bf16)));
-            if (!bf16) SSC_TRY(dev_alloc(h, (void**)&ls.wscale, (size_t)ls.spec.cout * 4));
             he = hipMemcpy(raw, weights[l], (size_t)9 * ls.spec.cin * ls.spec.cout * esz, hipMemcpyHostToDevice);
-            if (he == hipSuccess) he = launch_pack_weights(raw, ls.spec.cin, ls.spec.cout, bf16, fwd, ls.wscale, ls.wpack);
+            if (he == hipSuccess) he = launch_pack_weights(raw, ls.spec.cin, ls.spec.cout, bf16, ls.wpack);
             if (he != hipSuccess) { rc = hip_fail(he); goto fail; }
             H = ls.Hout;
             W = ls.Wout;
@@ -567,12 +551,11 @@ int create_impl(const sscater_grid* grid, int32_t batch, const sscater_layer* la
             us.Ws = src.Wout;
             us.coff = h->Cn;
             h->Cn += ups[u].cout;
-            SSC_TRY(dev_alloc(h, &us.wpack, up_wpack_bytes(us.cin, ups[u].cout, ups[u].stride)));
-            if (!bf16) SSC_TRY(dev_alloc(h, (void**)&us.wscale, (size_t)ups[u].cout * 4));
+            SSC_TRY(dev_alloc(h, &us.wpack, up_wpack_bytes(us.cin, ups[u].cout, ups[u].stride, bf16)));
             he = hipMemcpy(raw, up_weights[u],
                            (size_t)us.cin * ups[u].cout * ups[u].stride * ups[u].stride * esz, hipMemcpyHostToDevice);
             if (he == hipSuccess)
-                he = launch_pack_up_weights(raw, us.cin, ups[u].cout, ups[u].stride, bf16, fwd, us.wscale, us.wpack);
+                he = launch_pack_up_weights(raw, us.cin, ups[u].cout, ups[u].stride, bf16, us.wpack);
             if (he != hipSuccess) { rc = hip_fail(he); goto fail; }
         }
         SSC_TRY(dev_alloc(h, (void**)&h->Zn, (size_t)Hn * Wn * h->Cn * 4));
@@ -647,7 +630,6 @@ static int step_impl(sscater_t h, const sscater_pillars* pl, void* stream, bool 
     d.stamp0 = h->stamp0;
     d.count0 = h->a0_ptr(set);
     d.delta0 = h->delta0;
-    d.scale0 = h->dscale0;
     d.zero_ptr = h->set_ptr(set ^ 1);
     d.zero_n = h->nlines();
     d.clear = h->sparse ? nullptr : reinterpret_cast<uint4*>(h->flat[set ^ 1]);
@@ -832,7 +814,6 @@ int sscater_step_points(sscater_t h, const float* points, int32_t n_points, void
     f.res = p.res;
     f.X = h->X;
     f.delta0 = h->delta0;
-    f.scale0 = h->dscale0;
     f.tcount_clear = h->tcount + (size_t)pop * CSTRIDE;   // the next stride inserts into this slot
     f.err = h->err_dev;
     f.epoch = epoch;

@@ -20,9 +20,8 @@
 //
 // Layout: G = row_bytes / 16 lanes share one feature row, each lane moving 16
 // bytes, so a 64-channel fp32 row (256 B) is one fully coalesced 16-lane
-// access.  Delta rows (device_common.h): fp32 new - old in two fp16 planes, or
-// for bf16 the pair new, old that the layer kernels contract exactly (no delta
-// rounding).
+// access.  Delta rows (device_common.h): fp32 new - old, or for bf16 the pair
+// new, old that the layer kernels contract exactly (no delta rounding).
 #include "device_common.h"
 
 #include <algorithm>
@@ -41,7 +40,6 @@ __device__ __forceinline__ void emit_rows(const DetectArgs& a, int p, int pc, bo
     constexpr int G = ROWB / 16;
     constexpr int CL = BF16 ? 8 : 4;                // channels of a lane
     constexpr int C0 = ROWB / (BF16 ? 2 : 4);
-    constexpr int UL = G < 32 / CL ? G : 32 / CL;   // lanes of a unit of the delta row
     const int lane = lane_id();
     const int sub = lane % G;
     const int gbase = lane - sub;
@@ -62,29 +60,20 @@ __device__ __forceinline__ void emit_rows(const DetectArgs& a, int p, int pc, bo
     // (only a wavefront with a toggle loads them: the branch is uniform)
     const bool mtog = SPARSE && __ballot(tog && sub == 0) != 0ull;
     if (mtog) memb_issue(a.memb, pc, a.next.Hin, a.next.Win, tog && sub == 0, mb);
-    // fp32: the unit's scale, from all its lanes' values
-    f4v dn = {};
-    UnitScale us = {};
-    if constexpr (!BF16) {
-        dn.x = __uint_as_float(nv.x) - __uint_as_float(ov.x);
-        dn.y = __uint_as_float(nv.y) - __uint_as_float(ov.y);
-        dn.z = __uint_as_float(nv.z) - __uint_as_float(ov.z);
-        dn.w = __uint_as_float(nv.w) - __uint_as_float(ov.w);
-        uint32_t top = abs_bits4(dn);
-#pragma unroll
-        for (int k = 1; k < UL; k <<= 1) top = max(top, (uint32_t)__shfl_xor((int)top, k));
-        us = unit_scale(top);
-    }
     if (gd) {
         char* xrow = static_cast<char*>(a.X) + (size_t)pc * ROWB + sub * 16;
-        char* unit = static_cast<char*>(a.delta0) + (size_t)p * delta_row_bytes(C0) + (c0 / 32) * UNIT_BYTES +
-                     (c0 % 32) * 2;
+        char* drow = static_cast<char*>(a.delta0) + (size_t)p * delta_row_bytes(C0);
         if constexpr (BF16) {
-            *reinterpret_cast<uint4*>(unit) = nv;
-            *reinterpret_cast<uint4*>(unit + 64) = ov;
+            char* u = drow + c0 / 32 * UNIT_BYTES + c0 % 32 * 2;
+            *reinterpret_cast<uint4*>(u) = nv;
+            *reinterpret_cast<uint4*>(u + plane_bytes(C0)) = ov;
         } else {
-            store_split4<C0>(unit, dn, us, true);
-            if (sub % UL == 0) a.scale0[(size_t)p * units_of(C0) + c0 / 32] = us.inv;
+            f4v dn;
+            dn.x = __uint_as_float(nv.x) - __uint_as_float(ov.x);
+            dn.y = __uint_as_float(nv.y) - __uint_as_float(ov.y);
+            dn.z = __uint_as_float(nv.z) - __uint_as_float(ov.z);
+            dn.w = __uint_as_float(nv.w) - __uint_as_float(ov.w);
+            *reinterpret_cast<f4v*>(drow + c0 * 4) = dn;
         }
         *reinterpret_cast<uint4*>(xrow) = nv;
         if (sub == 0) a.stamp0[p] = a.epoch;

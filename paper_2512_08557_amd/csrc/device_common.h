@@ -282,154 +282,188 @@ __device__ __forceinline__ void clear_grid(uint4* p, int n) {
 
 // ---- delta rows ----
 //
-// A delta row is stored at its cell in units of 32 channels, 128 bytes each:
-// two planes of 32 16-bit values, so that one unit is both planes of one
-// K = 32 matrix instruction and a row has 4 bytes per channel in either dtype.
-// Rows of fewer than 32 channels take one unit whose other values stay zero.
-//   bf16: plane 0 holds bf16(phi(Z_new)), plane 1 bf16(phi(Z_old)); the
-//         consumers contract the difference of the two exactly.
-//   fp32: plane 0 holds hi = fp16(v * s), plane 1 lo = fp16(v * s - hi), where
-//         v is the fp32 delta and s the power of two that brings the unit's
-//         largest |v| into [2^14, 2^15); the unit's 1/s is kept beside the
-//         rows as a bf16 value (a power of two, so exact).  hi + lo carries v
-//         to 2^-24 of itself, half an fp32 ulp (2^-39 of the unit's largest
-//         value where that is more), and the weights are split the same way
-//         with a scale per output channel, so hi*hi + lo*hi + hi*lo on the
-//         fp16 matrix cores stands for the fp32 product at 3 matrix
-//         instructions per 32 channels instead of 8 of the fp32 kind.  Scales
-//         multiply fp32 sums only, by powers of two.
-//         A row of 16 channels leaves half of its unit free, which takes what
-//         the split leaves over (rest = v * s - hi - lo, at no cost to the
-//         consumers): plane 0 = [hi | rest], plane 1 = [lo | hi], against the
-//         weights' planes [Whi | Wrest] and [Wlo | Whi].  The short sums of 16
-//         channels are the ones where the split's error would show (3e-8 of
-//         the result beside the 9e-8 of the fp32 arithmetic around it).
-// A unit that holds a NaN or an infinity gets that as its 1/s (and +-1 at the
-// infinite values), so that what it contributes is not finite either.
+// A delta row is stored at its cell, 4 bytes per channel in either dtype:
+//   fp32: the fp32 deltas phi(Z_new) - phi(Z_old), consecutive channels.
+//   bf16: per 32 channels 64 bytes of bf16(phi(Z_new)), then 64 bytes of
+//         bf16(phi(Z_old)) (16 channels: 32 bytes each); the consumers
+//         contract the difference of the two exactly.
+// Consumers take a row in units of 32 channels (a row of 16 is one unit), 128
+// bytes, which is one K = 32 matrix instruction's range.
+//
+// fp32 on the bf16 matrix cores.  A consumer splits its fp32 values in
+// registers into three bf16 planes, h = bf16(v), m = bf16(v - h),
+// l = v - h - m: 8 significant bits each, so the three hold all 24 bits, and
+// with fp32's exponents, so values of any size stand beside each other (only
+// bits below 2^-133 are lost).  Weights come split the same way.  Six of the
+// nine products are formed; the other three are at most 2 * 2^-8 * 2^-17 +
+// 2^-34 of the whole, the size of an fp32 multiplication's one rounding.  Six bf16 instructions take 96 cycles for 32
+// channels where the fp32 kind takes 256.  The five smaller products of a unit
+// (at most 2^-7 of the first) are summed by themselves and added once, so a
+// unit costs the large sum two roundings, as little as it can on 16 registers
+// (a second set of sums for them took 32 and spilled).
+// Measured against fp16 planes under a power of two shared by 32 channels
+// (three products, but the planes hold 22 bits, and fewer for a channel far
+// below the unit's largest): 128->128 layer, one input channel in 10^9 times
+// the others with weights of 0, error 4e-4 of the result; here 1e-7.
 constexpr int UNIT_BYTES = 128;
 __host__ __device__ constexpr int units_of(int channels) { return channels > 32 ? channels / 32 : 1; }
-__host__ __device__ constexpr int delta_row_bytes(int channels) { return units_of(channels) * UNIT_BYTES; }
+__host__ __device__ constexpr int delta_row_bytes(int channels) { return 4 * channels; }
+// bytes from a bf16 row's new values to the old ones of the same channels
+__host__ __device__ constexpr int plane_bytes(int channels) { return channels < 32 ? 2 * channels : 64; }
 
-typedef _Float16 h8v __attribute__((ext_vector_type(8)));
-typedef _Float16 h4v __attribute__((ext_vector_type(4)));
+typedef float f2v __attribute__((ext_vector_type(2)));
+typedef __bf16 bf2v __attribute__((ext_vector_type(2)));
 
-__device__ __forceinline__ uint32_t abs_bits4(const f4v v) {
-    return max(max(__float_as_uint(v.x) & 0x7FFFFFFFu, __float_as_uint(v.y) & 0x7FFFFFFFu),
-               max(__float_as_uint(v.z) & 0x7FFFFFFFu, __float_as_uint(v.w) & 0x7FFFFFFFu));
+// Two values rounded to bf16 (nearest even), x in the low half.
+__device__ __forceinline__ uint32_t bf16_pair(float x, float y) {
+    const bf2v h = __builtin_convertvector((f2v{x, y}), bf2v);
+    uint32_t b;
+    __builtin_memcpy(&b, &h, 4);
+    return b;
 }
 
-// Scale of a unit whose largest |value| has the bits mb: the factor s, and
-// the bf16 bits of 1/s.
-struct UnitScale {
-    float s;
-    uint16_t inv;
-    bool finite;
+// The three planes of two values.  An infinity, and a finite value that rounds
+// to one in bf16, leave a NaN in the lower planes, so the sums they enter are
+// NaN.  SPECIAL does those right: an infinity goes to `inf` alone, and the
+// planes of such a large value are cut off instead of rounded (h + m stays
+// below it).  Every other value's planes are the same either way.
+template <bool SPECIAL>
+__device__ __forceinline__ void split_pair(float x, float y, uint32_t& h, uint32_t& m, uint32_t& l, uint32_t& inf) {
+    if constexpr (SPECIAL) {
+        const uint32_t xb = __float_as_uint(x), yb = __float_as_uint(y);
+        const bool xi = (xb & 0x7FFFFFFFu) == 0x7F800000u, yi = (yb & 0x7FFFFFFFu) == 0x7F800000u;
+        inf = (xi ? xb >> 16 : 0u) | (yi ? yb & 0xFFFF0000u : 0u);
+        x = xi ? 0.f : x;
+        y = yi ? 0.f : y;
+    }
+    h = bf16_pair(x, y);
+    bool xl = false, yl = false;
+    if constexpr (SPECIAL) {
+        xl = (h & 0x7FFFu) == 0x7F80u;
+        yl = (h & 0x7FFF0000u) == 0x7F800000u;
+        if (xl) h = (h & 0xFFFF0000u) | (__float_as_uint(x) >> 16);
+        if (yl) h = (h & 0xFFFFu) | (__float_as_uint(y) & 0xFFFF0000u);
+    }
+    const float rx = x - __uint_as_float(h << 16), ry = y - __uint_as_float(h & 0xFFFF0000u);
+    m = bf16_pair(rx, ry);
+    if constexpr (SPECIAL) {
+        if (xl) m = (m & 0xFFFF0000u) | (__float_as_uint(rx) >> 16);
+        if (yl) m = (m & 0xFFFFu) | (__float_as_uint(ry) & 0xFFFF0000u);
+    }
+    l = bf16_pair(rx - __uint_as_float(m << 16), ry - __uint_as_float(m & 0xFFFF0000u));
+}
+
+// The matrix operands of one lane's fp32 values of a unit: the four channels
+// 4*g .. +3 (a) and, of 32 channels, 16 + 4*g .. +3 (b).  Of 16 channels K
+// holds two planes side by side: x = [h | m], y = [h | l], and three
+// instructions form the six products.
+struct Planes {
+    uint4 x, y, z;            // h, m, l (16 channels: x and y as above)
+    uint4 inf;
 };
-__device__ __forceinline__ UnitScale unit_scale(uint32_t mb) {
-    UnitScale u;
-    const int e = (int)(mb >> 23);                    // biased exponent of the largest value
-    u.finite = e != 255;
-    const int se = min(268 - e, 253);                 // s = 2^(se - 127), 1/s a normal number
-    u.s = __uint_as_float((uint32_t)se << 23);
-    u.inv = (uint16_t)(u.finite ? (254 - se) << 7 : (mb > 0x7F800000u ? 0x7FC0 : 0x7F80));
-    return u;
-}
-
-// hi, lo and rest of a value under its unit's scale.
-__device__ __forceinline__ void split1(float v, const UnitScale& u, _Float16& hi, _Float16& lo, _Float16& rest) {
-    float t = v * u.s;
-    if (!u.finite) t = __builtin_isinf(v) ? copysignf(1.f, v) : 0.f;
-    hi = (_Float16)t;
-    lo = (_Float16)(t - (float)hi);
-    rest = (_Float16)(t - (float)hi - (float)lo);
-}
-
-// Four consecutive channels of a row of C channels into their places (p: the
-// first one's in plane 0).
-template <int C>
-__device__ __forceinline__ void store_split4(char* p, const f4v v, const UnitScale& u, bool store) {
-    h4v h, l, r;
+template <int CIN, bool SPECIAL>
+__device__ __forceinline__ Planes split_unit(const uint4 a, const uint4 b) {
+    Planes p = {};
+    uint32_t h[4], m[4], l[4], f[4] = {};
+    const uint32_t v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+    constexpr int N = CIN < 32 ? 2 : 4;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        _Float16 x, y, z;
-        split1(v[k], u, x, y, z);
-        h[k] = x;
-        l[k] = y;
-        r[k] = z;
+    for (int j = 0; j < N; ++j)
+        split_pair<SPECIAL>(__uint_as_float(v[2 * j]), __uint_as_float(v[2 * j + 1]), h[j], m[j], l[j], f[j]);
+    if constexpr (CIN < 32) {
+        p.x = make_uint4(h[0], h[1], m[0], m[1]);
+        p.y = make_uint4(h[0], h[1], l[0], l[1]);
+    } else {
+        p.x = make_uint4(h[0], h[1], h[2], h[3]);
+        p.y = make_uint4(m[0], m[1], m[2], m[3]);
+        p.z = make_uint4(l[0], l[1], l[2], l[3]);
     }
-    if (!store) return;
-    *reinterpret_cast<h4v*>(p) = h;
-    *reinterpret_cast<h4v*>(p + 64) = l;
-    if constexpr (C == 16) {
-        *reinterpret_cast<h4v*>(p + 32) = r;
-        *reinterpret_cast<h4v*>(p + 96) = h;
-    }
+    p.inf = make_uint4(f[0], f[1], f[2], f[3]);
+    return p;
 }
 
-__device__ __forceinline__ float bf16_to_f32(uint32_t b) { return __uint_as_float(b << 16); }
+__device__ __forceinline__ f4v mfma_bf16(const uint4 w, const uint4 v, const f4v c) {
+    bf8v W, V;
+    __builtin_memcpy(&W, &w, 16);
+    __builtin_memcpy(&V, &v, 16);
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(W, V, c, 0, 0, 0);
+}
+
+// One unit of one operand for NB blocks of 16 output channels; w0, w1, w2: the
+// weight planes Wh, Wm, Wl of every block (of 16 channels [Wh | Wh], [Wm |
+// Wh], [Wl | Wm]).  Products outer, blocks inner: an accumulator's
+// instructions are NB apart.
+template <int CIN, int NB, bool SPECIAL>
+__device__ __forceinline__ void mfma_unit(f4v (&acc)[NB], const uint4* w0, const uint4* w1, const uint4* w2,
+                                          const Planes& p) {
+    f4v lo[NB];
+#pragma unroll
+    for (int k = 0; k < NB; ++k) lo[k] = f4v{0.f, 0.f, 0.f, 0.f};
+    auto all = [&](f4v (&c)[NB], const uint4* w, const uint4 v) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < NB; ++k) c[k] = mfma_bf16(w[k], v, c[k]);
+    };
+    if constexpr (CIN < 32) {
+        all(lo, w2, p.x);
+        all(lo, w1, p.y);
+        all(acc, w0, p.x);
+    } else {
+        all(lo, w2, p.x);
+        all(lo, w1, p.y);
+        all(lo, w0, p.z);
+        all(lo, w1, p.x);
+        all(lo, w0, p.y);
+        all(acc, w0, p.x);
+    }
+#pragma unroll
+    for (int k = 0; k < NB; ++k)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[k][e] += lo[k][e];
+    if constexpr (SPECIAL) all(acc, w0, p.inf);
+}
 
 // Z update and next-layer delta row of one lane: output cell q, NBL blocks of
 // 16 output channels from channel c0 on, of which the lane holds the four at
-// 4*g (Z_new = Z_old + D; delta phi(Z_new) - phi(Z_old), see above).  The NBL
-// blocks are one unit (or all of a row of fewer than 32 channels), and the
-// lanes l, l^16, l^32, l^48 hold its channels of one cell: every lane of the
-// wavefront calls this, `store` says whether its cell and channels exist.
+// 4*g (Z_new = Z_old + D; delta phi(Z_new) - phi(Z_old), see above).
 // Sparse backbones: now / prev say whether the site is active in this and
 // in the previous stride; an inactive site's output is zero.
 template <int COUT, bool BF16, int NBL>
 __device__ __forceinline__ void epilogue_unit(const LayerArgs& a, int q, int c0, int g, const f4v (&o)[NBL],
-                                              const f4v (&d)[NBL], bool store, bool now, bool prev) {
-    f4v yo[NBL], yn[NBL];
+                                              const f4v (&d)[NBL], bool now, bool prev) {
+    char* drow = static_cast<char*>(a.delta_out) + (size_t)q * delta_row_bytes(COUT);
 #pragma unroll
     for (int i = 0; i < NBL; ++i) {
+        const int co = c0 + i * 16 + 4 * g;
         f4v zn;
 #pragma unroll
         for (int k = 0; k < 4; ++k) zn[k] = o[i][k] + d[i][k];
-        if (store) *reinterpret_cast<f4v*>(a.Z + (size_t)q * COUT + c0 + i * 16 + 4 * g) = zn;
-        yo[i] = o[i];
-        yn[i] = zn;
+        *reinterpret_cast<f4v*>(a.Z + (size_t)q * COUT + co) = zn;
+        if (!a.delta_out) continue;                       // uniform
+        f4v yo = o[i], yn = zn;
         if (a.relu) {
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                yo[i][k] = fmaxf(yo[i][k], 0.f);
-                yn[i][k] = fmaxf(yn[i][k], 0.f);
+                yo[k] = fmaxf(yo[k], 0.f);
+                yn[k] = fmaxf(yn[k], 0.f);
             }
         }
-        if (!prev) yo[i] = f4v{0.f, 0.f, 0.f, 0.f};
-        if (!now) yn[i] = f4v{0.f, 0.f, 0.f, 0.f};
-    }
-    if (!a.delta_out) return;                         // uniform
-    const int u = c0 / 32;
-    char* unit = static_cast<char*>(a.delta_out) + (size_t)q * delta_row_bytes(COUT) + u * UNIT_BYTES +
-                 (c0 % 32) * 2 + g * 8;
-    if constexpr (BF16) {
-#pragma unroll
-        for (int i = 0; i < NBL; ++i) {
+        if (!prev) yo = f4v{0.f, 0.f, 0.f, 0.f};
+        if (!now) yn = f4v{0.f, 0.f, 0.f, 0.f};
+        if constexpr (BF16) {
             uint2 pn, po;
-            pn.x = f32_to_bf16_bits(yn[i].x) | (f32_to_bf16_bits(yn[i].y) << 16);
-            pn.y = f32_to_bf16_bits(yn[i].z) | (f32_to_bf16_bits(yn[i].w) << 16);
-            po.x = f32_to_bf16_bits(yo[i].x) | (f32_to_bf16_bits(yo[i].y) << 16);
-            po.y = f32_to_bf16_bits(yo[i].z) | (f32_to_bf16_bits(yo[i].w) << 16);
-            if (store) {
-                *reinterpret_cast<uint2*>(unit + i * 32) = pn;
-                *reinterpret_cast<uint2*>(unit + 64 + i * 32) = po;
-            }
+            pn.x = f32_to_bf16_bits(yn.x) | (f32_to_bf16_bits(yn.y) << 16);
+            pn.y = f32_to_bf16_bits(yn.z) | (f32_to_bf16_bits(yn.w) << 16);
+            po.x = f32_to_bf16_bits(yo.x) | (f32_to_bf16_bits(yo.y) << 16);
+            po.y = f32_to_bf16_bits(yo.z) | (f32_to_bf16_bits(yo.w) << 16);
+            char* u = drow + co / 32 * UNIT_BYTES + co % 32 * 2;
+            *reinterpret_cast<uint2*>(u) = pn;
+            *reinterpret_cast<uint2*>(u + plane_bytes(COUT)) = po;
+        } else {
+            f4v dy;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) dy[k] = yn[k] - yo[k];
+            *reinterpret_cast<f4v*>(drow + co * 4) = dy;
         }
-    } else {
-        f4v dy[NBL];
-        uint32_t mb = 0u;
-#pragma unroll
-        for (int i = 0; i < NBL; ++i) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) dy[i][k] = yn[i][k] - yo[i][k];
-            mb = max(mb, abs_bits4(dy[i]));
-        }
-        mb = max(mb, (uint32_t)__shfl_xor((int)mb, 16));
-        mb = max(mb, (uint32_t)__shfl_xor((int)mb, 32));
-        const UnitScale us = unit_scale(mb);
-#pragma unroll
-        for (int i = 0; i < NBL; ++i) store_split4<COUT>(unit + i * 32, dy[i], us, store);
-        if (store && g == 0) a.scale_out[(size_t)q * units_of(COUT) + u] = us.inv;
     }
 }
 

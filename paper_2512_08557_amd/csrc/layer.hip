@@ -38,29 +38,31 @@
 //     downsampling) is built by the launch's first workgroups (plan.h), or in
 //     sparse backbones, where it depends on the active sets, by the tiles.
 //
-// MFMA operand layout (v_mfma_f32_16x16x32_f16 / _bf16):
+// MFMA operand layout (v_mfma_f32_16x16x32_bf16):
 //   src0 = weights, lane l supplies row cout = l%16, k = 8*(l/16) .. +7;
 //   src1 = deltas,  lane l supplies cell l%16,       k = 8*(l/16) .. +7;
 //   D: lane l, register j holds cout 4*(l/16)+j of cell l%16.
-// A unit (32 channels, 128 bytes: two 64-byte planes, device_common.h) is
-// exactly one such k range of both planes.
-//   fp32: P = hi.Whi + hi.Wlo + lo.Whi over the unit, acc += P / s(unit);
-//         the output channel's weight scale is applied once at the end;
+// A unit (32 channels, 128 bytes) is one such k range, of which a lane reads
+// the 16-byte pieces l/16 and 4 + l/16:
+//   fp32: channels 4*(l/16) .. +3 and 16 more, split in registers into three
+//         bf16 planes, six products (device_common.h);
 //   bf16: acc += new.W - old.W (the sign bits of the old plane flipped:
 //         exact), so the weights move once.
 //
 // What bounds it: at one sensor's sparsity the chain launch -> list entry ->
 // stamps -> operands -> sums -> Z; on long lists the copies, at 64 bytes per
-// clock and compute unit (a 32 x 64 tile of a 256-channel layer takes 864 KB,
-// 5.8 us).  Measured per launch against what ran before (fp32 matrix
+// clock and compute unit, and in fp32 the matrix instructions beside them (a
+// 32 x 64 tile of a 256-channel fp32 layer takes 1.2 MB, 7.7 us, and 5.8 us of
+// instructions).  Measured per fp32 launch against what ran before (fp32 matrix
 // instructions; the wide layers as a contraction plus a tap sum), 432x496
-// backbone, ~4300 / 2300 / 1000 output cells: 64->64 11.5 -> 6.8 us, 128->128
-// 9.9 + 5.8 -> 10.0, 256->256 14.5 + 5.6 -> 13.9; the first window (all cells)
-// 48 -> 27, 38 + 20 -> 30.5, 40 + 10 -> 27.7; four 1024x1024 images 64->64
-// 70.7 -> 37.7.  With the
+// backbone, ~4300 / 2300 / 1000 output cells: 64->64 11.5 -> 7.8 us, 128->128
+// 9.9 + 5.8 -> 10.6, 256->256 14.5 + 5.6 -> 14.2; the first window (all cells)
+// 48 -> 28, 38 + 20 -> 31.4, 40 + 10 -> 34.1; four 1024x1024 images 64->64
+// 70.7 -> 36.8.  Two fp16 planes and three products, which hold fewer bits
+// (device_common.h), took 6.5, 9.9 and 13.4 us for the first three.  With the
 // same tile as a workgroup-wide ring of LDS stages instead (both operands
-// shared, a barrier per stage) a 256->256 launch took 21.9 us, and with the
-// delta rows loaded in operand order straight into registers 17.6.
+// shared, a barrier per stage) a 256->256 launch took 8.5 us more, and with
+// the delta rows loaded in operand order straight into registers 4.2.
 //
 // Sparse backbones (SPARSE = true): a site inactive in this and in the
 // previous stride neither changes nor propagates; an inactive site's output is
@@ -74,42 +76,62 @@
 
 namespace ssc {
 
-template <int CIN, int COUT, bool BF16, int TM = 32>
+template <int CIN, int COUT, bool BF16, bool SPARSE, int TM = 32>
 struct LayerShape {
     static constexpr int U = units_of(CIN);              // units of a delta row
     static constexpr int MH = TM / 16;
     static constexpr int CPU = TM / 8;                   // copies of a unit (1 KB each)
-    static constexpr int ROWB = U * UNIT_BYTES;
+    static constexpr int ROWB = delta_row_bytes(CIN);
     static constexpr int NT = COUT >= 64 ? 64 : (COUT + 15) / 16 * 16;   // output channels per workgroup
     static constexpr int NBN = COUT > 64 ? COUT / 64 : 1;                // workgroups per tile
     static constexpr int NB = NT / 16;                   // 16-channel blocks
-    static constexpr int PL = BF16 ? 1 : 2;              // weight planes
+    static constexpr int PL = BF16 ? 1 : 3;              // weight planes
     static constexpr int WU = NT * 64 * PL;              // bytes of a weight unit
     static constexpr int NU = 9 * U;                     // units of a tile
-    static constexpr int NW = U >= 4 ? 8 : 6;            // wavefronts
+    // wavefronts: 64 dense fp32 channels' 18 units leave a SIMD at most 5 of
+    // them with 8 wavefronts, 6 with 6 (four 1024x1024 images 278 -> 270 us a
+    // stride); the sparse kernels spill more registers with 8 (253 -> 259 us)
+    static constexpr int NW = U >= 4 || (U == 2 && !BF16 && !SPARSE) ? 8 : 6;
     static constexpr int CNT = (NU + NW - 1) / NW;       // units of a wavefront, at most
     static constexpr int FULL = NU / NW;                 // units every wavefront has
     static constexpr bool STAT = U <= (BF16 ? 4 : 2);    // weights stay in registers
-    static constexpr int D = CNT < 3 ? CNT : 3;          // units whose loads are in flight
+    // units whose copies are in flight (two where LDS takes eight wavefronts'
+    // and a weight plane)
+    static constexpr int D = U == 2 && !BF16 && !SPARSE ? 2 : (CNT < 3 ? CNT : 3);
+    // units whose weights are: of three fp32 planes two units' are what the
+    // registers hold beside the sums
+    static constexpr int DW = STAT ? CNT : (BF16 || D < 2 ? D : 2);
+    // 64 fp32 channels: the planes Wl of a wavefront's three units stay in LDS
+    // (72 KB a workgroup), Wh and Wm in registers (96); five of the six
+    // products are formed from those
+    static constexpr bool WLDS = STAT && !BF16 && U == 2;
+    static constexpr int RP = WLDS ? 2 : PL;             // weight planes in registers
+    static constexpr int WL_LDS = WLDS ? NU * NB * 1024 : 16;
     // vector loads certainly issued after the copies of unit i and before it
-    // is awaited: the copies of the next D - 1 units and the streamed weights
-    // of those of them that every wavefront has (the weights of the first D
-    // units come before all copies; a unit's own weights and those of a unit
-    // that only some wavefronts compute are not counted, the compiler may place
-    // them on either side of the wait).  A smaller count waits for more.
+    // is awaited: first the copies of units 0 .. D - 1 (the weights of units 0
+    // .. DW - 1 come before them), then, behind each unit x, the copies of unit
+    // x + D and the streamed weights of unit x + DW.  Weights of a unit that
+    // only some wavefronts compute are not counted, the compiler may place them
+    // on either side of the wait.  A smaller count waits for more.
     static constexpr int younger(int i) {
         int n = 0;
-        for (int j = i + 1; j < i + D && j < CNT; ++j) n += CPU + (!STAT && j >= D && j < FULL ? PL * NB : 0);
+        for (int j = i + 1; j < D; ++j) n += CPU;
+        for (int x = i < D ? 0 : i - D; x < i; ++x) {
+            if (x + D > i && x + D < CNT) n += CPU;
+            if (!STAT && x + DW < FULL) n += PL * NB;
+        }
         return n;
     }
-    static constexpr int MAXW = (D - 1) * (CPU + PL * NB);
+    static constexpr int MAXW = (D - 1) * CPU + (STAT ? 0 : D * PL * NB);
     // finishing wavefronts: 16 cells and one unit of output channels each (all
     // the channels of a tile of fewer than 64)
     static constexpr int OB = NB == 4 ? 2 : NB;          // blocks
     static constexpr int FW = MH * (NB / OB);
     static constexpr int SLOT = TM * UNIT_BYTES;         // a wavefront's unit in LDS
     static constexpr int SB = SLOT / 1024;               // blocks of partial sums that fit in it
-    static constexpr int PLAN_LDS = PLAN_IN * 4 + PLAN_WORDS * (int)sizeof(PlanWord);
+    // LDS of the workgroup: the plan and tiles of either height take the same
+    static constexpr int AS = NW * SLOT, AS2 = D > 2 ? AS : 16;   // a slot of every wavefront
+    static_assert(TM < 32 || (AS >= PLAN_IN * 4 && AS >= PLAN_WORDS * (int)sizeof(PlanWord)), "the plan fits");
 };
 
 // The tiles of TM cells of one workgroup; b: its number among the grid's
@@ -117,19 +139,20 @@ struct LayerShape {
 template <int CIN, int COUT, int S, bool BF16, bool SPARSE, bool SPREAD, int TM>
 __device__ __forceinline__ void layer_tiles(const int32_t* __restrict__ plist, const uint16_t* __restrict__ ptaps,
                                             const char* __restrict__ pweights, int pcap, int n0, int n1, int b, int nwg,
-                                            const LayerArgs& a) {
-    using L = LayerShape<CIN, COUT, BF16, TM>;
+                                            const LayerArgs& a, int (&rowcell)[9][32],
+                                            char (&as0)[LayerShape<CIN, COUT, BF16, SPARSE>::AS],
+                                            char (&as1)[LayerShape<CIN, COUT, BF16, SPARSE>::AS],
+                                            char (&as2)[LayerShape<CIN, COUT, BF16, SPARSE>::AS2],
+                                            char (&wl)[LayerShape<CIN, COUT, BF16, SPARSE>::WL_LDS]) {
+    // rowcell: changed input cell, or -1.  as0, as1, as2: the wavefronts' delta
+    // units in flight (one LDS array per slot: the compiler then tracks the
+    // copies into each slot separately); at the end slots 0 and 1 take the
+    // partial sums.  wl: weight planes (WLDS).
+    using L = LayerShape<CIN, COUT, BF16, SPARSE, TM>;
     constexpr int U = L::U, NB = L::NB, NBN = L::NBN, OB = L::OB, NW = L::NW, CNT = L::CNT, D = L::D, PL = L::PL;
     constexpr int NTH = 64 * NW, MH = L::MH, SLOT = L::SLOT, SB = L::SB;
+    constexpr int DW = L::DW, RP = L::RP;
     static_assert(9 * TM <= NTH, "one table entry per thread");
-    __shared__ int rowcell[9][TM];                                      // changed input cell, or -1
-    __shared__ __attribute__((aligned(16))) uint16_t rowsc[BF16 ? 1 : 9][TM][U];     // its units' 1/s (bf16), or 0
-    // the wavefronts' delta units in flight (one LDS array per slot: the
-    // compiler then tracks the copies into each slot separately); at the end
-    // slots 0 and 1 take the partial sums
-    __shared__ __attribute__((aligned(1024))) char as0[NW * SLOT];
-    __shared__ __attribute__((aligned(1024))) char as1[NW * SLOT];
-    __shared__ __attribute__((aligned(1024))) char as2[D > 2 ? NW * SLOT : 16];
     const int tid = (int)threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int cl = lane & 15, g = lane >> 4;
@@ -160,7 +183,14 @@ __device__ __forceinline__ void layer_tiles(const int32_t* __restrict__ plist, c
     // slot l % 8 of it (piece ^ (row / 2) % 8: the 16 rows read together then
     // fall in different banks); reads: rows 16m + cl, piece g of either plane
     const int cr = lane >> 3;
-    const uint32_t cp0 = (uint32_t)(((lane & 7) ^ (cr >> 1)) * 16), cp1 = cp0 ^ 64u;   // even and odd k
+    uint32_t cp0 = (uint32_t)(((lane & 7) ^ (cr >> 1)) * 16), cp1 = cp0 ^ 64u;   // even and odd k
+    // rows of 16 channels hold 64 bytes: fp32 reads pieces 0 to 3 only, bf16
+    // pieces 0, 1 (new) and 4, 5 (old) with zeros in the others
+    const bool half = BF16 && CIN < 32 && (cp0 & 32u) != 0u;
+    if constexpr (CIN < 32) {
+        cp0 = BF16 ? (cp0 & 64u) / 2 + (cp0 & 16u) : cp0 & 63u;
+        cp1 = BF16 ? (cp1 & 64u) / 2 + (cp1 & 16u) : cp1 & 63u;
+    }
     const int sa = (cl >> 1) & 7;
     int a_hi = w * SLOT + cl * UNIT_BYTES + ((g ^ sa) << 4), a_lo = a_hi ^ 64;
     // (single values: the compiler's copy tracking follows only a short
@@ -172,18 +202,27 @@ __device__ __forceinline__ void layer_tiles(const int32_t* __restrict__ plist, c
     const char* wbase = pweights + (size_t)nb * L::NU * L::WU;   // uniform
     const uint32_t wl16 = (uint32_t)lane * 16u;
     // weights of unit un
-    auto load_w = [&](int un, uint4 (&bw)[PL * NB]) __attribute__((always_inline)) {
+    auto load_w = [&](int un, uint4 (&bw)[RP * NB]) __attribute__((always_inline)) {
         const char* p = wbase + (size_t)un * L::WU;
 #pragma unroll
-        for (int k = 0; k < PL * NB; ++k) bw[k] = *reinterpret_cast<const uint4*>(p + k * 1024 + wl16);
+        for (int k = 0; k < RP * NB; ++k) bw[k] = *reinterpret_cast<const uint4*>(p + k * 1024 + wl16);
     };
     // unit i of wavefront ww (a wavefront without an i-th unit loads the last)
     auto unit = [&](int ww, int i) __attribute__((always_inline)) { return min(ww + NW * i, L::NU - 1); };
-    constexpr int NBUF = L::STAT ? CNT : D;
-    uint4 bw[NBUF][PL * NB];
+    uint4 bw[DW][RP * NB];
     if (tile * TM < n) {
 #pragma unroll
-        for (int i = 0; i < NBUF; ++i) load_w(unit(w, i), bw[i]);
+        for (int i = 0; i < DW; ++i)
+            if (!L::STAT || i < L::FULL || w + NW * i < L::NU) load_w(unit(w, i), bw[i]);
+        if constexpr (L::WLDS) {
+#pragma unroll
+            for (int i = 0; i < CNT; ++i)
+                if (i < L::FULL || w + NW * i < L::NU)
+#pragma unroll
+                    for (int k = 0; k < NB; ++k)
+                        copy16(wbase + (size_t)unit(w, i) * L::WU + (2 * NB + k) * 1024 + wl16,
+                               (lds_char*)wl + (unit(w, i) * NB + k) * 1024);
+        }
     }
 
     if (a.cum_dst && b == 0)
@@ -196,12 +235,11 @@ __device__ __forceinline__ void layer_tiles(const int32_t* __restrict__ plist, c
         int wt = w;
         asm volatile("" : "+s"(wt));
         const int ef = t0 + 16 * fm + cl;                // the lane's cell of the epilogue
-        const int qf = seg[min(ef, n - 1)];
+        const int q = seg[min(ef, n - 1)];               // a valid cell also past the segment's end
         const bool vt = t0 + tr < n, vrow = ef < n;
-        const int q = qf;                                // a valid cell also past the segment's end
 
-        // this thread's input cell, whether it changed, and its units' scales
-        // (loads from clamped, always valid addresses)
+        // this thread's input cell and whether it changed (loads from clamped,
+        // always valid addresses)
         const int q0 = __builtin_amdgcn_readfirstlane(qt);   // row 0, always valid
         const int p = vt ? qt : q0;
         int cell = 0;
@@ -220,17 +258,7 @@ __device__ __forceinline__ void layer_tiles(const int32_t* __restrict__ plist, c
             cell = img * (a.Hin * a.Win) + min(max(ir, 0), a.Hin - 1) * a.Win + min(max(ic, 0), a.Win - 1);
             if (!tseg) ev = a.stamp_in[cell];
         }
-        uint32_t sc[BF16 ? 1 : (U + 1) / 2];
-        if constexpr (!BF16) {
-            const uint16_t* sp = a.scale_in + (size_t)cell * U;
-            if constexpr (U == 1) {
-                sc[0] = *sp;
-            } else {
-#pragma unroll
-                for (int i = 0; i < U / 2; ++i) sc[i] = reinterpret_cast<const uint32_t*>(sp)[i];
-            }
-        }
-        f4v zo[OB], wsc[OB];
+        f4v zo[OB];
         // sparse backbones: only a site active now or before can change, and
         // only such sites go to the next layer's list
         bool now = true, prev = true;
@@ -241,7 +269,6 @@ __device__ __forceinline__ void layer_tiles(const int32_t* __restrict__ plist, c
             for (int i = 0; i < OB; ++i) {
                 const int co = min(c0 + i * 16 + 4 * g, COUT - 4);
                 zo[i] = *reinterpret_cast<const f4v*>(a.Z + (size_t)q * COUT + co);
-                if constexpr (!BF16) wsc[i] = *reinterpret_cast<const f4v*>(a.wscale + co);
             }
             if constexpr (SPARSE) {
                 const uint64_t mw = a.memb[q];
@@ -251,20 +278,6 @@ __device__ __forceinline__ void layer_tiles(const int32_t* __restrict__ plist, c
         }
         ch = ch && ev == a.epoch;
         if (tt < 9) rowcell[tt][tr] = ch ? cell : -1;
-        auto put_scales = [&]() __attribute__((always_inline)) {
-            if constexpr (!BF16) {
-                if (tt < 9) {
-                    uint16_t* sp = &rowsc[tt][tr][0];
-                    if constexpr (U == 1) {
-                        *sp = ch ? (uint16_t)sc[0] : 0;
-                    } else {
-#pragma unroll
-                        for (int i = 0; i < U / 2; ++i) reinterpret_cast<uint32_t*>(sp)[i] = ch ? sc[i] : 0u;
-                    }
-                }
-            }
-        };
-        if constexpr (SPARSE) put_scales();              // they came with the stamps
         // the next tile's entry
         qt = seg[min((tile + GT) * TM + tr, pcap - 1)];
         if (tseg) mk = tseg[min((tile + GT) * TM + tr, pcap - 1)];
@@ -276,16 +289,12 @@ __device__ __forceinline__ void layer_tiles(const int32_t* __restrict__ plist, c
 #pragma unroll
             for (int k = 0; k < L::CPU; ++k) {
                 const int rc = rowcell[t][8 * k + cr];
-                const char* src = rc >= 0 ? dbase + (size_t)rc * L::ROWB + u * UNIT_BYTES : zrow;
+                const char* src = rc >= 0 && !half ? dbase + (size_t)rc * L::ROWB + u * UNIT_BYTES : zrow;
                 copy16(src + (k & 1 ? cp1 : cp0), st + wt * SLOT + k * 1024);
             }
         };
 #pragma unroll
         for (int i = 0; i < D; ++i) load_a(i, slot(i));
-        if constexpr (!BF16 && !SPARSE) {                // the scales arrive while the copies are in flight
-            put_scales();
-            lds_barrier();
-        }
         // sparse: the next layer's footprint stamps go out behind the first
         // operands, its list positions are taken once those have arrived (the
         // counter's round trip overlaps the contraction); a regular layer
@@ -297,12 +306,14 @@ __device__ __forceinline__ void layer_tiles(const int32_t* __restrict__ plist, c
         PropSlots<4> ps;
 
         f4v acc[MH][NB];
+        auto clear_sums = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int m = 0; m < MH; ++m)
+            for (int m = 0; m < MH; ++m)
 #pragma unroll
-            for (int i = 0; i < NB; ++i) acc[m][i] = f4v{0.f, 0.f, 0.f, 0.f};
-        auto compute = [&](int i, const lds_char* st, const uint4 (&bv)[PL * NB]) __attribute__((always_inline)) {
-            const int un = unit(wt, i), t = un / U, u = un - t * U;
+                for (int i = 0; i < NB; ++i) acc[m][i] = f4v{0.f, 0.f, 0.f, 0.f};
+        };
+        clear_sums();
+        auto compute = [&](int i, const lds_char* st, const uint4 (&bv)[RP * NB]) __attribute__((always_inline)) {
             uint4 av[2 * MH];
 #pragma unroll
             for (int m = 0; m < MH; ++m) {
@@ -329,30 +340,14 @@ __device__ __forceinline__ void layer_tiles(const int32_t* __restrict__ plist, c
                         acc[m][k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(B, O, acc[m][k], 0, 0, 0);
                     }
                 } else {
-                    const float s = bf16_to_f32(rowsc[t][16 * m + cl][u]);
-                    h8v A, O, B;
-                    __builtin_memcpy(&A, &av[2 * m], 16);
-                    __builtin_memcpy(&O, &av[2 * m + 1], 16);
-                    f4v P[NB];
+                    uint4 w3[NB];
 #pragma unroll
                     for (int k = 0; k < NB; ++k) {
-                        __builtin_memcpy(&B, &bv[NB + k], 16);
-                        P[k] = __builtin_amdgcn_mfma_f32_16x16x32_f16(B, A, f4v{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+                        if constexpr (L::WLDS) w3[k] = lds16((lds_char*)wl + (unit(wt, i) * NB + k) * 1024 + wl16);
+                        else w3[k] = bv[2 * NB + k];
                     }
-#pragma unroll
-                    for (int k = 0; k < NB; ++k) {
-                        __builtin_memcpy(&B, &bv[k], 16);
-                        P[k] = __builtin_amdgcn_mfma_f32_16x16x32_f16(B, O, P[k], 0, 0, 0);
-                    }
-#pragma unroll
-                    for (int k = 0; k < NB; ++k) {
-                        __builtin_memcpy(&B, &bv[k], 16);
-                        P[k] = __builtin_amdgcn_mfma_f32_16x16x32_f16(B, A, P[k], 0, 0, 0);
-                    }
-#pragma unroll
-                    for (int k = 0; k < NB; ++k)
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) acc[m][k][j] = fmaf(P[k][j], s, acc[m][k][j]);
+                    mfma_unit<CIN, NB, false>(acc[m], bv, bv + NB, w3,
+                                              split_unit<CIN, false>(av[2 * m], av[2 * m + 1]));
                 }
             }
         };
@@ -370,17 +365,53 @@ __device__ __forceinline__ void layer_tiles(const int32_t* __restrict__ plist, c
                     // a use outside the branch: the loads of a unit that only
                     // some wavefronts compute stay where they were issued
 #pragma unroll
-                    for (int k = 0; k < PL * NB; ++k) pin(bw[i % D][k]);
+                    for (int k = 0; k < PL * NB; ++k) pin(bw[i % DW][k]);
                 }
-            if (i < L::FULL || wt + NW * i < L::NU) compute(i, slot(i % D), bw[L::STAT ? i : i % D]);
+            if (i < L::FULL || wt + NW * i < L::NU) compute(i, slot(i % D), bw[i % DW]);
             if (i + D < CNT) {
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the slot has been read
                 load_a(i + D, slot(i % D));
-                if constexpr (!L::STAT) load_w(unit(wt, i + D), bw[i % D]);
             }
+            if constexpr (!L::STAT)
+                if (i + DW < CNT) load_w(unit(wt, i + DW), bw[i % DW]);
             if (i == 0 && lead && a.has_next) prop_reserve<4>(a.next, a.epoch, shard, pb, ps);
             // keep the scheduler from hoisting later loads past this unit
             __builtin_amdgcn_sched_barrier(0);
+        }
+
+        if constexpr (!BF16) {
+            // a value that the planes don't carry (an infinity, or a finite one
+            // that rounds to it in bf16) left a NaN in all of its cell's sums:
+            // the wavefront's units again, with such values done right
+            bool nan = false;
+#pragma unroll
+            for (int m = 0; m < MH; ++m) nan = nan || acc[m][0][0] != acc[m][0][0];
+            if (__ballot(nan) != 0ull) {
+                clear_sums();
+#pragma unroll 1
+                for (int un = wt; un < L::NU; un += NW) {
+                    const int t = un / U, u = un - t * U;
+#pragma unroll
+                    for (int m = 0; m < MH; ++m) {
+                        const int rc = rowcell[t][16 * m + cl];
+                        const char* src = rc >= 0 ? dbase + (size_t)rc * L::ROWB + u * UNIT_BYTES : zrow;
+                        const uint4 v = *reinterpret_cast<const uint4*>(src + g * 16);
+                        const uint4 x = *reinterpret_cast<const uint4*>(src + g * 16 + (CIN < 32 ? 0 : 64));
+                        const Planes pl = split_unit<CIN, true>(v, x);
+#pragma unroll
+                        for (int k = 0; k < NB; ++k) {
+                            uint4 wk[PL];
+#pragma unroll
+                            for (int p = 0; p < PL; ++p)
+                                wk[p] = *reinterpret_cast<const uint4*>(wbase + (size_t)un * L::WU +
+                                                                        (p * NB + k) * 1024 + wl16);
+                            f4v s[1] = {acc[m][k]};
+                            mfma_unit<CIN, 1, true>(s, wk, wk + 1, wk + 2, pl);
+                            acc[m][k] = s[0];
+                        }
+                    }
+                }
+            }
         }
 
         // partial sums, added in wavefront order by the finishing wavefronts
@@ -405,11 +436,8 @@ __device__ __forceinline__ void layer_tiles(const int32_t* __restrict__ plist, c
 #pragma unroll
                     for (int e = 0; e < 4; ++e) d[i][e] += x[e];
                 }
-                if constexpr (!BF16)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) d[i][j] *= wsc[i][j];
             }
-            epilogue_unit<COUT, BF16, OB>(a, q, c0, g, zo, d, vrow && (COUT % 16 == 0 || 4 * g < COUT), now, prev);
+            if (vrow && (COUT % 16 == 0 || 4 * g < COUT)) epilogue_unit<COUT, BF16, OB>(a, q, c0, g, zo, d, now, prev);
         }
         if (SPREAD && lead) memb_finish(a.mnext, q, a.Hout, a.Wout, mbt, now ? 1 : -1, a.epoch);
         if (lead && a.has_next) prop_write<4>(a.next, shard, pb, ps);
@@ -419,7 +447,7 @@ __device__ __forceinline__ void layer_tiles(const int32_t* __restrict__ plist, c
         if constexpr (!L::STAT) {
             if ((tile + GT) * TM < n) {
 #pragma unroll
-                for (int i = 0; i < D; ++i) load_w(unit(wt, i), bw[i]);
+                for (int i = 0; i < DW; ++i) load_w(unit(wt, i), bw[i]);
             }
         }
     }
@@ -430,37 +458,45 @@ __device__ __forceinline__ void layer_tiles(const int32_t* __restrict__ plist, c
 // bits, counts, weights) and the branch to the plan need not wait for the
 // argument fetch, a round trip of its own.
 //
-// Tile height: 32 cells, so that a tile's share of the weights is small; up to
-// 64 input channels 16 where the list then still has a workgroup for every
-// tile, on twice the compute units with half the operands and sums each.
-// Measured on a 432x496 stride, 16 against 32 cells: 64->128 stride-2 launch
-// (45 32-cell tiles) 6.3 against 7.7 us, 64->64 (100 to 140 tiles) 7.0 against
-// 8.0 us; on lists of more tiles than workgroups 16 cells lose (four 1024x1024
-// images, 1500 tiles: 45 against 33 us, two workgroups per compute unit).
+// Tile height: 32 cells, so that a tile's share of the weights is small; 16
+// where the list then still has a workgroup for every tile, on twice the
+// compute units with half the operands and sums each (bf16 up to 64 input
+// channels: wider bf16 tiles are all weight copies).  Measured on a 432x496
+// fp32 stride, 16 against 32 cells: 128->128 10.6 against 10.7 us, 256->256
+// 14.2 against 16.6, 128->256 stride 2 8.9 against 10.8, the backbone 205.6
+// against 222.6; with two fp16 planes 64->128 stride 2 (45 32-cell tiles) 6.3
+// against 7.7 us, 64->64 (100 to 140 tiles) 7.0 against 8.0.  On lists of more
+// tiles than workgroups 16 cells lose (four 1024x1024 images, 1500 tiles: 45
+// against 33 us, two workgroups per compute unit).
 template <int CIN, int COUT, int S, bool BF16, bool SPARSE, bool SPREAD>
-__global__ __launch_bounds__((64 * LayerShape<CIN, COUT, BF16>::NW)) void layer_kernel(
+__global__ __launch_bounds__((64 * LayerShape<CIN, COUT, BF16, SPARSE>::NW)) void layer_kernel(
     const int32_t* __restrict__ plist, const int32_t* __restrict__ pcount, const uint16_t* __restrict__ ptaps,
     const char* __restrict__ pweights, int pcap, int pplan, LayerArgs a) {
-    using L = LayerShape<CIN, COUT, BF16>;
+    using L = LayerShape<CIN, COUT, BF16, SPARSE>;
+    __shared__ int rowcell[9][32];
+    __shared__ __attribute__((aligned(1024))) char as0[L::AS];
+    __shared__ __attribute__((aligned(1024))) char as1[L::AS];
+    __shared__ __attribute__((aligned(1024))) char as2[L::AS2];
+    __shared__ __attribute__((aligned(1024))) char wl[L::WL_LDS];
     if constexpr (!SPARSE) {
         if ((int)blockIdx.x < pplan) {
-            __shared__ __attribute__((aligned(16))) char planlds[L::PLAN_LDS];
-            __shared__ int plansum[2 * L::NW + 2];
-            plan_tile<L::NW>(a.plan, a.epoch, (int)blockIdx.x, reinterpret_cast<uint32_t*>(planlds),
-                             reinterpret_cast<PlanWord*>(planlds + PLAN_IN * 4), plansum);
+            plan_tile<L::NW>(a.plan, a.epoch, (int)blockIdx.x, reinterpret_cast<uint32_t*>(as0),
+                             reinterpret_cast<PlanWord*>(as1), &rowcell[0][0]);
             return;
         }
     }
     const int nplan = SPARSE ? 0 : pplan;
     const int b = (int)blockIdx.x - nplan, nwg = (int)gridDim.x - nplan;
     const int n0 = pcount[0], n1 = pcount[CSTRIDE];
-    if constexpr (L::U <= 2) {
+    if constexpr (L::U <= 2 || !BF16) {
         if (max(n0, n1) <= 16 * (nwg / (2 * L::NBN))) {
-            layer_tiles<CIN, COUT, S, BF16, SPARSE, SPREAD, 16>(plist, ptaps, pweights, pcap, n0, n1, b, nwg, a);
+            layer_tiles<CIN, COUT, S, BF16, SPARSE, SPREAD, 16>(plist, ptaps, pweights, pcap, n0, n1, b, nwg, a, rowcell,
+                                                                as0, as1, as2, wl);
             return;
         }
     }
-    layer_tiles<CIN, COUT, S, BF16, SPARSE, SPREAD, 32>(plist, ptaps, pweights, pcap, n0, n1, b, nwg, a);
+    layer_tiles<CIN, COUT, S, BF16, SPARSE, SPREAD, 32>(plist, ptaps, pweights, pcap, n0, n1, b, nwg, a, rowcell, as0,
+                                                        as1, as2, wl);
 }
 
 // ---------------------------------------------------------------------------
@@ -484,7 +520,7 @@ bool layer_supported(int cin, int cout, int stride, bool /*bf16*/) {
 
 template <int CI, int CO, int S, bool BF16, bool SPARSE>
 static hipError_t launch_shape(const LayerArgs& a, const LaunchCtx& c) {
-    using L = LayerShape<CI, CO, BF16>;
+    using L = LayerShape<CI, CO, BF16, SPARSE>;
     // one workgroup per compute unit (a longer list loops over its remaining
     // tiles), at most the tiles of a full list
     const long long most = ((long long)a.cap + 15) / 16 * 2 * L::NBN;
@@ -516,116 +552,96 @@ hipError_t launch_layer(const LayerArgs& a, int cin, int cout, int stride, bool 
 // ---------------------------------------------------------------------------
 // Both kernels' packed weights: [output groups][unit][plane][block of 16
 // output channels][lane l][8], lane l holding output channel l%16 of the block
-// and the unit's input channels 8*(l/16) .. +7 (zero past cin, except as
-// device_common.h says for 16 fp32 channels).  bf16: one
-// plane (two for an upsampler: W and -W, an exact sign flip); fp32: the hi
-// plane, then the lo plane, of the weights scaled per output channel by the
-// power of two that brings the largest into [2^14, 2^15), as delta units are;
-// scale[co] is its inverse (or the NaN or infinity among the weights).
-
-// One wavefront per output channel: the scale of its n weights, the j-th at
-// w[(j / run) * step + co * run + j % run] (run consecutive values each).
-__global__ __launch_bounds__(64) void weight_scale_kernel(const float* __restrict__ w, int n, int run, int step,
-                                                          float* __restrict__ fwd, float* __restrict__ inv) {
-    const int co = (int)blockIdx.x;
-    uint32_t mb = 0u;
-    for (int j = (int)threadIdx.x; j < n; j += 64)
-        mb = max(mb, __float_as_uint(w[(size_t)(j / run) * step + (size_t)co * run + j % run]) & 0x7FFFFFFFu);
-#pragma unroll
-    for (int k = 1; k < 64; k <<= 1) mb = max(mb, (uint32_t)__shfl_xor((int)mb, k));
-    if (threadIdx.x == 0) {
-        const UnitScale u = unit_scale(mb);
-        fwd[co] = u.finite ? u.s : 0.f;
-        inv[co] = bf16_to_f32(u.inv);
-    }
+// and, at e = 0 .. 7, the unit's input channel
+//   bf16: 8*(l/16) + e (zero past cin); one plane (two for an upsampler: W and
+//         -W, an exact sign flip);
+//   fp32: 4*(l/16) + e%4, and 16 more for e >= 4, the order in which a lane
+//         takes its delta row (split_unit); planes Wh, Wm, Wl, or of 16
+//         channels [Wh | Wh], [Wm | Wh], [Wl | Wm] over the halves of e.
+__device__ __forceinline__ int packed_channel(int cin, int unit, int l, int e, int bf16) {
+    if (bf16) return unit * 32 + (l >> 4) * 8 + e;
+    return unit * 32 + (l >> 4) * 4 + (e & 3) + (cin >= 32 ? (e >> 2) * 16 : 0);
 }
 
-// Plane values at input channel k of a unit (k = 0..31) of an fp32 weight w
-// under its channel's scale s (0: the channel holds a value that is not
-// finite).  cin = 16: k >= 16 stands for channel k - 16 (device_common.h).
-__device__ __forceinline__ void split_weight(float w, float s, bool upper, uint16_t& p0, uint16_t& p1) {
-    const UnitScale u{s, 0, s != 0.f};
-    _Float16 hi, lo, rest;
-    split1(w, u, hi, lo, rest);
-    const _Float16 a = upper ? rest : hi, b = upper ? hi : lo;
-    __builtin_memcpy(&p0, &a, 2);
-    __builtin_memcpy(&p1, &b, 2);
+// An fp32 weight's planes at position e of a unit.
+__device__ __forceinline__ void split_weight(float w, int cin, int e, uint16_t (&p)[3]) {
+    uint32_t h, m, l, inf;
+    split_pair<true>(w, 0.f, h, m, l, inf);
+    const uint16_t H = (uint16_t)(h | inf), M = (uint16_t)m;
+    const bool upper = cin < 32 && e >= 4;
+    p[0] = H;
+    p[1] = upper ? H : M;
+    p[2] = upper ? M : (uint16_t)l;
 }
 
 // OIHW [cout][cin][3][3]; groups of up to 64 output channels, units [tap][32
 // input channels].  One thread per packed position of a plane; positions of no
-// channel (cout = 8, cin = 16) keep the buffer's zeros.
+// channel (cout = 8, bf16 cin = 16) keep the buffer's zeros.
 __global__ __launch_bounds__(256) void pack_weights_kernel(const void* __restrict__ w, int cin, int cout, int bf16,
-                                                           const float* __restrict__ fwd, uint16_t* __restrict__ out) {
+                                                           uint16_t* __restrict__ out) {
     const int nu = units_of(cin), coutp = (cout + 15) / 16 * 16, nt = min(coutp, 64);
     const int plane = nt * 32;                            // values of a plane of a unit
     const int n = 9 * nu * coutp * 32;
     for (int i = (int)(blockIdx.x * 256 + threadIdx.x); i < n; i += (int)gridDim.x * 256) {
         const int e = i & 7, l = (i >> 3) & 63, blk = i % plane / 512, ug = i / plane;   // ug: group and unit
         const int group = ug / (9 * nu), un = ug - group * (9 * nu), t = un / nu, u = un - t * nu;
-        const int co = group * nt + blk * 16 + (l & 15);
-        int ci = u * 32 + (l >> 4) * 8 + e;
-        const bool upper = !bf16 && cin == 16 && ci >= 16;
-        if (upper) ci -= 16;
+        const int co = group * nt + blk * 16 + (l & 15), ci = packed_channel(cin, u, l, e, bf16);
         if (co >= cout || ci >= cin) continue;
         const size_t from = ((size_t)co * cin + ci) * 9 + t;
-        const size_t to = (size_t)ug * plane * (bf16 ? 1 : 2) + (i % plane);
-        if (bf16) out[to] = static_cast<const uint16_t*>(w)[from];
-        else split_weight(static_cast<const float*>(w)[from], fwd[co], upper, out[to], out[to + plane]);
+        const size_t to = (size_t)ug * plane * (bf16 ? 1 : 3) + (i % plane);
+        if (bf16) {
+            out[to] = static_cast<const uint16_t*>(w)[from];
+        } else {
+            uint16_t p[3];
+            split_weight(static_cast<const float*>(w)[from], cin, e, p);
+            for (int k = 0; k < 3; ++k) out[to + (size_t)k * plane] = p[k];
+        }
     }
 }
 
 // [cin][cout][S][S]; one group, units [32 input channels], blocks [sub-cell
 // a*S + b][16 output channels].
 __global__ __launch_bounds__(256) void pack_up_weights_kernel(const void* __restrict__ w, int cin, int cout, int s2,
-                                                              int bf16, const float* __restrict__ fwd,
-                                                              uint16_t* __restrict__ out) {
+                                                              int bf16, uint16_t* __restrict__ out) {
     const int ncbt = cout / 16, plane = s2 * cout * 32;
     const int n = units_of(cin) * plane;
     for (int i = (int)(blockIdx.x * 256 + threadIdx.x); i < n; i += (int)gridDim.x * 256) {
         const int e = i & 7, l = (i >> 3) & 63, ob = i % plane / 512, u = i / plane;
-        const int ab = ob / ncbt, co = (ob - ab * ncbt) * 16 + (l & 15);
-        int ci = u * 32 + (l >> 4) * 8 + e;
-        const bool upper = !bf16 && cin == 16 && ci >= 16;
-        if (upper) ci -= 16;
+        const int ab = ob / ncbt, co = (ob - ab * ncbt) * 16 + (l & 15), ci = packed_channel(cin, u, l, e, bf16);
         if (ci >= cin) continue;
         const size_t from = ((size_t)ci * cout + co) * s2 + ab;
-        const size_t to = (size_t)u * plane * 2 + (i % plane);
+        const size_t to = (size_t)u * plane * (bf16 ? 2 : 3) + (i % plane);
         if (bf16) {
             const uint16_t v = static_cast<const uint16_t*>(w)[from];
             out[to] = v;
             out[to + plane] = v ^ 0x8000u;
         } else {
-            split_weight(static_cast<const float*>(w)[from], fwd[co], upper, out[to], out[to + plane]);
+            uint16_t p[3];
+            split_weight(static_cast<const float*>(w)[from], cin, e, p);
+            for (int k = 0; k < 3; ++k) out[to + (size_t)k * plane] = p[k];
         }
     }
 }
 
 size_t wpack_bytes(int cin, int cout, bool bf16) {
-    return (size_t)9 * units_of(cin) * (size_t)((cout + 15) / 16 * 16) * (bf16 ? 64 : 128);
+    return (size_t)9 * units_of(cin) * (size_t)((cout + 15) / 16 * 16) * 64 * (bf16 ? 1 : 3);
 }
 
-size_t up_wpack_bytes(int cin, int cout, int stride) {
-    return (size_t)units_of(cin) * 2 * (size_t)cout * stride * stride * 64;
+size_t up_wpack_bytes(int cin, int cout, int stride, bool bf16) {
+    return (size_t)units_of(cin) * (size_t)cout * stride * stride * 64 * (bf16 ? 2 : 3);
 }
 
 static unsigned pack_grid(size_t values) { return (unsigned)std::min<size_t>(1024, (values + 255) / 256); }
 
-hipError_t launch_pack_weights(const void* w, int cin, int cout, bool bf16, float* fwd, float* inv, void* out) {
-    if (!bf16) hipLaunchKernelGGL(weight_scale_kernel, dim3(cout), dim3(64), 0, nullptr, static_cast<const float*>(w),
-                                  9 * cin, 9 * cin, 0, fwd, inv);
+hipError_t launch_pack_weights(const void* w, int cin, int cout, bool bf16, void* out) {
     hipLaunchKernelGGL(pack_weights_kernel, dim3(pack_grid(wpack_bytes(cin, cout, true) / 2)), dim3(256), 0, nullptr, w,
-                       cin, cout, bf16 ? 1 : 0, fwd, static_cast<uint16_t*>(out));
+                       cin, cout, bf16 ? 1 : 0, static_cast<uint16_t*>(out));
     return hipGetLastError();
 }
 
-hipError_t launch_pack_up_weights(const void* w, int cin, int cout, int stride, bool bf16, float* fwd, float* inv,
-                                  void* out) {
-    const int s2 = stride * stride;
-    if (!bf16) hipLaunchKernelGGL(weight_scale_kernel, dim3(cout), dim3(64), 0, nullptr, static_cast<const float*>(w),
-                                  cin * s2, s2, cout * s2, fwd, inv);
-    hipLaunchKernelGGL(pack_up_weights_kernel, dim3(pack_grid(up_wpack_bytes(cin, cout, stride) / 4)), dim3(256), 0,
-                       nullptr, w, cin, cout, s2, bf16 ? 1 : 0, fwd, static_cast<uint16_t*>(out));
+hipError_t launch_pack_up_weights(const void* w, int cin, int cout, int stride, bool bf16, void* out) {
+    hipLaunchKernelGGL(pack_up_weights_kernel, dim3(pack_grid(up_wpack_bytes(cin, cout, stride, true) / 4)), dim3(256),
+                       0, nullptr, w, cin, cout, stride * stride, bf16 ? 1 : 0, static_cast<uint16_t*>(out));
     return hipGetLastError();
 }
 

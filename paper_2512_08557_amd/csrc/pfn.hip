@@ -204,32 +204,16 @@ __global__ __launch_bounds__(256) void pfn_kernel(PfnArgs a) {
             f = fmaxf(f, v);
         }
 
-        // the delta row: channel `lane` of unit lane / 32
-        const int units = a.C0 > 32 ? 2 : 1;
-        char* unit = static_cast<char*>(a.delta0) + ((size_t)c * units + (lane >> 5)) * UNIT_BYTES + (lane & 31) * 2;
-        if constexpr (BF16) {
-            if (lane < a.C0) {
+        if (lane < a.C0) {
+            char* drow = static_cast<char*>(a.delta0) + (size_t)c * delta_row_bytes(a.C0);
+            if constexpr (BF16) {
+                char* u = drow + (lane >> 5) * UNIT_BYTES + (lane & 31) * 2;
                 const uint16_t nb = (uint16_t)f32_to_bf16_bits(f);
-                *reinterpret_cast<uint16_t*>(unit) = nb;
-                *reinterpret_cast<uint16_t*>(unit + 64) = xo_b;
+                *reinterpret_cast<uint16_t*>(u) = nb;
+                *reinterpret_cast<uint16_t*>(u + plane_bytes(a.C0)) = xo_b;
                 static_cast<uint16_t*>(a.X)[(size_t)c * a.C0 + lane] = nb;
-            }
-        } else {
-            const float dv = lane < a.C0 ? f - xo_f : 0.f;
-            uint32_t mb = __float_as_uint(dv) & 0x7FFFFFFFu;
-#pragma unroll
-            for (int k = 1; k < 32; k <<= 1) mb = max(mb, (uint32_t)__shfl_xor((int)mb, k));
-            const UnitScale us = unit_scale(mb);
-            if (lane < a.C0) {
-                _Float16 hi, lo, rest;
-                split1(dv, us, hi, lo, rest);
-                *reinterpret_cast<_Float16*>(unit) = hi;
-                *reinterpret_cast<_Float16*>(unit + 64) = lo;
-                if (a.C0 == 16) {
-                    *reinterpret_cast<_Float16*>(unit + 32) = rest;
-                    *reinterpret_cast<_Float16*>(unit + 96) = hi;
-                }
-                if ((lane & 31) == 0) a.scale0[(size_t)c * units + (lane >> 5)] = us.inv;
+            } else {
+                reinterpret_cast<float*>(drow)[lane] = f - xo_f;
                 static_cast<float*>(a.X)[(size_t)c * a.C0 + lane] = f;
             }
         }

@@ -121,7 +121,6 @@ struct DetectArgs {
     uint32_t* stamp0;     // change stamps of the input grid [H0*W0]
     int32_t* count0;      // |A_0| (statistics only): segment k, XCD x at count0[(k * PSPREAD + x) * CSTRIDE]
     void* delta0;         // input delta rows, dense by cell
-    uint16_t* scale0;     // fp32: their units' scales, dense by cell [H0*W0][units]
     int32_t* zero_ptr;    // counters to clear for the next stride (may be nullptr)
     int32_t zero_n;       // their lines (word 0 of each CSTRIDE line is the counter)
     uint4* clear;         // the next stride's bitmap of the first layer's list, cleared here (may be nullptr)
@@ -135,21 +134,18 @@ struct DetectArgs {
 
 // One convolution layer: contraction of the input deltas with the weights,
 // update of the persistent pre-activation map, activation delta epilogue and
-// propagation of the change list to the next layer.  Delta rows and their
-// scales: see device_common.h.
+// propagation of the change list to the next layer.  Delta rows: see
+// device_common.h.
 struct LayerArgs {
     const int32_t* list;        // A_l: NSHARD segments of `cap` cells of the output grid
     const int32_t* count;       // segment lengths, segment k at count[k * CSTRIDE]
     int cap;                    // capacity of a segment (cells of the output grid)
     const uint32_t* stamp_in;   // change stamps of the input grid [Hin*Win]
     const void* delta_in;       // input delta rows, dense by cell
-    const uint16_t* scale_in;   // fp32: their units' scales [Hin*Win][units]
     const void* zero;           // a zero row, read for an unchanged input
     const void* wpack;          // weights repacked for the MFMA operand layout
-    const float* wscale;        // fp32: scale of each output channel's sums
     float* Z;                   // persistent pre-activation map [Hout*Wout][cout]
     void* delta_out;            // output delta rows, dense by cell (nullptr: last layer)
-    uint16_t* scale_out;        // fp32: their units' scales
     int Hin, Win, Hout, Wout;
     int relu;
     uint32_t epoch;
@@ -176,9 +172,7 @@ struct UpArgs {
     const int32_t* count;       // segment lengths, segment k at count[k * CSTRIDE]
     int cap;                    // cells of the source grid
     const void* delta_src;      // source delta rows, dense by cell
-    const uint16_t* scale_src;  // fp32: their units' scales
     const void* wpack;          // weights repacked for the MFMA operand layout
-    const float* wscale;        // fp32: scale of each output channel's sums
     float* Z;                   // neck pre-activation map [Hn*Wn][ctot]
     int ctot, coff;             // channels of the neck map, first channel of this upsampler
     uint32_t* stamp;            // change stamps of the neck grid [Hn*Wn]
@@ -234,7 +228,6 @@ struct PfnArgs {
     float x_min, y_min, res;
     void* X;                    // canvas [H*W][C0] (grid dtype)
     void* delta0;               // input delta rows, dense by cell
-    uint16_t* scale0;           // fp32: their units' scales
     int32_t* tcount_clear;      // counter of the next stride's insertion slot, cleared here
     int32_t* err;
     uint32_t epoch;
@@ -294,13 +287,11 @@ bool upsample_supported(int cin, int cout, int stride);
 hipError_t launch_upsample(const UpArgs& a, int cin, int cout, int stride, bool bf16, const LaunchCtx& c);
 // Weights in the layouts the kernels read (see layer.hip), packed on the device
 // (null stream) from the caller's: OIHW, or [cin][cout][S][S] of an upsampler.
-// fwd: cout floats of scratch, inv: what each output channel's sums are
-// multiplied by (both fp32 only); out: zeroed.
+// out: zeroed.
 size_t wpack_bytes(int cin, int cout, bool bf16);
-size_t up_wpack_bytes(int cin, int cout, int stride);
-hipError_t launch_pack_weights(const void* w, int cin, int cout, bool bf16, float* fwd, float* inv, void* out);
-hipError_t launch_pack_up_weights(const void* w, int cin, int cout, int stride, bool bf16, float* fwd, float* inv,
-                                  void* out);
+size_t up_wpack_bytes(int cin, int cout, int stride, bool bf16);
+hipError_t launch_pack_weights(const void* w, int cin, int cout, bool bf16, void* out);
+hipError_t launch_pack_up_weights(const void* w, int cin, int cout, int stride, bool bf16, void* out);
 // Buffers to clear (bytes a multiple of 16: all library buffers are padded to
 // 256); at most FILL_MAX, enough for every buffer of a handle.
 constexpr int FILL_MAX = 80, FILL_CHUNK = 4096;   // 16-byte values per chunk

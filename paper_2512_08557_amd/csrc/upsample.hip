@@ -22,16 +22,22 @@
 #include "device_common.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace ssc {
 
 template <int CIN, int COUT, int S, bool BF16>
 struct UpShape {
     static constexpr int NU = units_of(CIN);
-    static constexpr int NCH = 2 * NU;                    // 1 KB operand chunks: both planes of every unit
+    static constexpr int PL = BF16 ? 2 : 3;               // weight planes: W and -W, or of fp32 three (device_common.h)
+    // 1 KB operand chunks: both halves of every unit (bf16: its planes; 16
+    // fp32 channels are one chunk)
+    static constexpr int NCH = !BF16 && CIN < 32 ? 1 : 2 * NU;
     static constexpr int NCBT = COUT / 16;
     static constexpr int NOB = S * S * NCBT;              // output blocks per input cell
-    static constexpr int BPW = NOB >= 8 ? 2 : 1;          // output blocks per wavefront
+    // output blocks per wavefront (the three planes of two blocks of 256
+    // channels are 192 registers, one workgroup per compute unit)
+    static constexpr int BPW = NOB >= 8 && (BF16 || NU < 8) ? 2 : 1;
     static constexpr int OBG = (NOB + 4 * BPW - 1) / (4 * BPW);   // workgroups per tile
 };
 
@@ -39,7 +45,7 @@ template <int CIN, int COUT, int S, bool BF16>
 __global__ __launch_bounds__(256) void upsample_kernel(UpArgs a) {
     using U = UpShape<CIN, COUT, S, BF16>;
     constexpr int NCH = U::NCH, NOB = U::NOB, NCBT = U::NCBT, BPW = U::BPW, OBG = U::OBG;
-    constexpr int NU = U::NU, ROWB = delta_row_bytes(CIN);
+    constexpr int NU = U::NU, PL = U::PL, ROWB = delta_row_bytes(CIN);
     __shared__ uint4 As0[NCH][64];
     __shared__ uint4 As1[NCH][64];
 
@@ -51,7 +57,10 @@ __global__ __launch_bounds__(256) void upsample_kernel(UpArgs a) {
     const int TG = (int)gridDim.x / (OBG * NSHARD);        // workgroups per (segment, block group)
     const int32_t* seg = a.list + (size_t)shard * a.cap;
     const int n = a.count[shard * CSTRIDE];
-    const char* dbase = static_cast<const char*>(a.delta_src) + g * 16;
+    // chunk c of a lane's row (16 bf16 channels: 32 bytes a plane, the lanes
+    // past them copy those again)
+    constexpr int CB = BF16 ? plane_bytes(CIN) : 64;
+    const char* dbase = static_cast<const char*>(a.delta_src) + (CB == 64 ? g : g & 1) * 16;
     const uint4* wbase = static_cast<const uint4*>(a.wpack) + lane;
     const int Wn = S * a.Wsrc;
 
@@ -64,12 +73,12 @@ __global__ __launch_bounds__(256) void upsample_kernel(UpArgs a) {
         ob[k] = obv[k] ? o : 0;
     }
     // this wavefront's weights, for every tile
-    uint4 bw[BPW][NCH];
+    uint4 bw[BPW][PL * NU];
     if ((b / OBG) / NSHARD * 16 < n) {
 #pragma unroll
         for (int k = 0; k < BPW; ++k)
 #pragma unroll
-            for (int c = 0; c < NCH; ++c) bw[k][c] = wbase[((size_t)c * NOB + ob[k]) * 64];
+            for (int c = 0; c < PL * NU; ++c) bw[k][c] = wbase[((size_t)c * NOB + ob[k]) * 64];
     }
 
     // tiles tile0, tile0 + TG, ...: the next tile's delta rows (into the other
@@ -94,33 +103,16 @@ __global__ __launch_bounds__(256) void upsample_kernel(UpArgs a) {
     };
     int tile = (b / OBG) / NSHARD;
     int pc = 0, pn = 0;        // cells of this lane's row in this tile and the next
-    f4v zo[BPW], wsc[BPW];
-    // fp32: the row's unit scales (two per word; one unit: the low half)
-    constexpr int SW = BF16 ? 1 : (NU + 1) / 2;
-    uint32_t sc[SW] = {};
-    auto scales = [&](int p, uint32_t (&s)[SW]) __attribute__((always_inline)) {
-        if constexpr (!BF16) {
-            const uint16_t* sp = a.scale_src + (size_t)p * NU;
-            if constexpr (NU == 1) s[0] = *sp;
-            else
-#pragma unroll
-                for (int i = 0; i < SW; ++i) s[i] = reinterpret_cast<const uint32_t*>(sp)[i];
-        }
-    };
+    f4v zo[BPW];
     if (tile * 16 < n) {
         pc = entry(tile);
 #pragma unroll
         for (int c = wave; c < NCH; c += 4)
             __builtin_amdgcn_global_load_lds(
-                (const __attribute__((address_space(1))) void*)(dbase + (size_t)pc * ROWB + c * 64),
+                (const __attribute__((address_space(1))) void*)(dbase + (size_t)pc * ROWB + c * CB),
                 (__attribute__((address_space(3))) void*)&As0[c][0], 16, 0, 0);
 #pragma unroll
         for (int k = 0; k < BPW; ++k) zo[k] = *reinterpret_cast<const f4v*>(z_at(out_cell(pc, k), k));
-        scales(pc, sc);
-        if constexpr (!BF16)
-#pragma unroll
-            for (int k = 0; k < BPW; ++k)
-                wsc[k] = *reinterpret_cast<const f4v*>(a.wscale + (ob[k] - (ob[k] / NCBT) * NCBT) * 16 + 4 * g);
         pn = entry(tile + TG);
     }
     // one tile from `cur`, the next one's rows into `nxt`; false past the end
@@ -131,60 +123,57 @@ __global__ __launch_bounds__(256) void upsample_kernel(UpArgs a) {
         __syncthreads();                                   // this tile's chunks have landed; `nxt` is free
         const bool more = (tile + TG) * 16 < n;
         f4v zn_next[BPW];
-        uint32_t sc_next[SW] = {};
         int pnn = 0;
         if (more) {
 #pragma unroll
             for (int c = wave; c < NCH; c += 4)
                 __builtin_amdgcn_global_load_lds(
-                    (const __attribute__((address_space(1))) void*)(dbase + (size_t)pn * ROWB + c * 64),
+                    (const __attribute__((address_space(1))) void*)(dbase + (size_t)pn * ROWB + c * CB),
                     (__attribute__((address_space(3))) void*)&nxt[c][0], 16, 0, 0);
 #pragma unroll
             for (int k = 0; k < BPW; ++k) zn_next[k] = *reinterpret_cast<const f4v*>(z_at(out_cell(pn, k), k));
-            scales(pn, sc_next);
             pnn = entry(tile + 2 * TG);
         }
         f4v acc[BPW];
+        auto clear_sums = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int k = 0; k < BPW; ++k) acc[k] = f4v{0.f, 0.f, 0.f, 0.f};
+            for (int k = 0; k < BPW; ++k) acc[k] = f4v{0.f, 0.f, 0.f, 0.f};
+        };
+        clear_sums();
+        if constexpr (BF16) {
 #pragma unroll
-        for (int u = 0; u < NU; ++u) {
-            const uint4 av = cur[2 * u][lane], ov = cur[2 * u + 1][lane];
-            if constexpr (BF16) {
-                bf8v A, O;
-                __builtin_memcpy(&A, &av, 16);
-                __builtin_memcpy(&O, &ov, 16);
-#pragma unroll
-                for (int k = 0; k < BPW; ++k) {
-                    bf8v B, N;
-                    __builtin_memcpy(&B, &bw[k][2 * u], 16);
-                    __builtin_memcpy(&N, &bw[k][2 * u + 1], 16);
-                    acc[k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(B, A, acc[k], 0, 0, 0);
-                    acc[k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(N, O, acc[k], 0, 0, 0);
-                }
-            } else {
-                h8v A, O;
-                __builtin_memcpy(&A, &av, 16);
-                __builtin_memcpy(&O, &ov, 16);
-                const float s = bf16_to_f32((sc[u / 2] >> (16 * (u & 1))) & 0xFFFFu);
+            for (int u = 0; u < NU; ++u) {
+                uint4 av = cur[2 * u][lane], ov = cur[2 * u + 1][lane];
+                if (CIN < 32 && g >= 2) av = ov = make_uint4(0u, 0u, 0u, 0u);
 #pragma unroll
                 for (int k = 0; k < BPW; ++k) {
-                    h8v H, Lw;
-                    __builtin_memcpy(&H, &bw[k][2 * u], 16);
-                    __builtin_memcpy(&Lw, &bw[k][2 * u + 1], 16);
-                    f4v P = __builtin_amdgcn_mfma_f32_16x16x32_f16(Lw, A, f4v{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
-                    P = __builtin_amdgcn_mfma_f32_16x16x32_f16(H, O, P, 0, 0, 0);
-                    P = __builtin_amdgcn_mfma_f32_16x16x32_f16(H, A, P, 0, 0, 0);
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) acc[k][j] = fmaf(P[j], s, acc[k][j]);
+                    acc[k] = mfma_bf16(bw[k][2 * u], av, acc[k]);
+                    acc[k] = mfma_bf16(bw[k][2 * u + 1], ov, acc[k]);
                 }
             }
+        } else {
+            auto contract = [&](auto special) __attribute__((always_inline)) {
+#pragma unroll
+                for (int u = 0; u < NU; ++u) {
+                    const Planes p = split_unit<CIN, decltype(special)::value>(cur[NCH == 1 ? 0 : 2 * u][lane],
+                                                                              cur[NCH == 1 ? 0 : 2 * u + 1][lane]);
+                    uint4 w0[BPW], w1[BPW], w2[BPW];
+#pragma unroll
+                    for (int k = 0; k < BPW; ++k) {
+                        w0[k] = bw[k][3 * u];
+                        w1[k] = bw[k][3 * u + 1];
+                        w2[k] = bw[k][3 * u + 2];
+                    }
+                    mfma_unit<CIN, BPW, decltype(special)::value>(acc, w0, w1, w2, p);
+                }
+            };
+            contract(std::false_type());
+            // values the planes don't carry (device_common.h)
+            if (__ballot(acc[0][0] != acc[0][0]) != 0ull) {
+                clear_sums();
+                contract(std::true_type());
+            }
         }
-        if constexpr (!BF16)
-#pragma unroll
-            for (int k = 0; k < BPW; ++k)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[k][j] *= wsc[k][j];
         if (vrow) {
 #pragma unroll
             for (int k = 0; k < BPW; ++k) {
@@ -202,8 +191,6 @@ __global__ __launch_bounds__(256) void upsample_kernel(UpArgs a) {
         if (more) {
 #pragma unroll
             for (int k = 0; k < BPW; ++k) zo[k] = zn_next[k];
-#pragma unroll
-            for (int i = 0; i < SW; ++i) sc[i] = sc_next[i];
         }
         pc = pn;
         pn = pnn;

@@ -1,7 +1,7 @@
 """Single layers at the sizes where the layer kernel's tiling and its split
 fp32 operands can go wrong: list lengths around whole tiles, every channel
-count, both strides, values far from 1, per-channel scales far apart, and
-values that are not finite."""
+count, both strides, values far from 1, output and input channels of scales far
+apart, single products, and values that are not finite or nearly so."""
 import numpy as np
 import pytest
 import torch
@@ -46,13 +46,15 @@ def _conv(x, w, stride):
 
 def _check(eng, wins, w, cin, stride, dtype, H, W, where):
     """|gpu - exact| per output, after the windows in turn.  Each stride adds a
-    sum of K = 9*cin products to every touched cell.  fp32: a product of two
-    split values is off by at most 3 * 2^-23 of itself, and summing takes at
-    most one rounding per matrix instruction's 32 products, channel unit and
-    wavefront (counted as 3 per unit, plus 16), 2^-24 each of the sum of
-    magnitudes.  bf16 products are exact, and the output is rounded to bf16."""
+    sum of K = 9*cin products to every touched cell.  fp32: the three planes
+    hold a value exactly, h within 2^-8 of it and h + m within 2^-17, so
+    the products left out (m*l, l*m, l*l) are at most 2^-24 + 2^-34 of the whole;
+    summing takes at most three roundings per channel unit (its large products,
+    its small ones, their sum) and one per wavefront and for Z (16 in all), 2^-24
+    each of the sum of magnitudes.  bf16 products are exact, and the output is
+    rounded to bf16."""
     units = 9 * max(1, cin // 32)
-    eps = (0 if dtype == "bf16" else 3 * 2.0 ** -23) + (3 * units + 16) * 2.0 ** -24
+    eps = (0 if dtype == "bf16" else 2.0 ** -24 + 2.0 ** -34) + (3 * units + 16) * 2.0 ** -24
     xs = [_canvas(x, cin, H, W) for x in wins]
     ref = _conv(xs[-1], w, stride)
     mag = sum(_conv(np.abs(a) + np.abs(b), np.abs(w), stride) for a, b in zip([0 * xs[0]] + xs[:-1], xs))
@@ -115,6 +117,88 @@ def test_magnitudes(cin, fscale, wscale):
     _check(eng, wins, w, cin, 1, "f32", H, W, f"cin {cin} features {fscale} weights {wscale}")
 
 
+def _unlike(rng, cin, spread):
+    """2^0 .. 2^spread over the input channels, in any order."""
+    return np.exp2(np.linspace(0, spread, cin) - spread / 2)[rng.permutation(cin)].astype(np.float32)
+
+
+@pytest.mark.parametrize("cin", [16, 32, 64, 128, 256])
+@pytest.mark.parametrize("spread", [12, 24, 30, 60])
+def test_input_channels_of_unlike_scale(cin, spread):
+    """Features 2^spread apart between the channels of a unit, weights the other
+    way round, so that every channel counts alike in the sums."""
+    H, W = 37, 41
+    rng = np.random.default_rng(cin + spread)
+    s = _unlike(rng, cin, spread)
+    w = (rng.standard_normal((32, cin, 3, 3)) / s[None, :, None, None]).astype(np.float32)
+    eng = _layer(cin, 32, 1, "f32", w, H, W)
+    wins = [_window(rng, n, cin, H, W, 1.0, "f32") for n in (500, 60)]
+    for _idx, f in wins:
+        f *= s
+    for win in wins:
+        _step(eng, win, "f32", True)
+    _check(eng, wins, w, cin, 1, "f32", H, W, f"cin {cin} spread 2^{spread}")
+
+
+@pytest.mark.parametrize("cin", [16, 64, 128])
+@pytest.mark.parametrize("ratio", [1e5, 1e7, 1e9, 1e20])
+def test_a_large_input_channel_of_weight_zero(cin, ratio):
+    H, W = 37, 41
+    rng = np.random.default_rng(cin)
+    w = rng.standard_normal((32, cin, 3, 3)).astype(np.float32)
+    w[:, 3] = 0.0
+    w[5, 7] *= ratio                                        # and one large weight, of a channel that is zero
+    eng = _layer(cin, 32, 1, "f32", w, H, W)
+    wins = [_window(rng, n, cin, H, W, 1.0, "f32") for n in (500, 60)]
+    for _idx, f in wins:
+        f[:, 3] *= ratio
+        f[:, 7] = 0.0
+    for win in wins:
+        _step(eng, win, "f32", True)
+    _check(eng, wins, w, cin, 1, "f32", H, W, f"cin {cin} ratio {ratio}")
+
+
+@pytest.mark.parametrize("cin", [16, 32, 128])
+def test_single_products(cin):
+    """One channel of one pillar under every output: what is read is one fp32
+    product, off by the products left out and a few roundings."""
+    H, W = 37, 41
+    rng = np.random.default_rng(cin)
+    w = rng.standard_normal((64, cin, 3, 3)).astype(np.float32)
+    eng = _layer(cin, 64, 1, "f32", w, H, W)
+    idx = np.array([(r * W + c) for r in range(1, H, 3) for c in range(1, W, 3)], np.int32)
+    f = np.zeros((len(idx), cin), np.float32)
+    f[np.arange(len(idx)), rng.integers(0, cin, len(idx))] = rng.standard_normal(len(idx))
+    _step(eng, (idx, f), "f32", True)
+    out = eng.read(1)
+    torch.cuda.synchronize()
+    got, ref = out.cpu().numpy().astype(np.float64), _conv(_canvas((idx, f), cin, H, W), w, 1)
+    assert np.all(np.abs(got - ref) <= 3 * 2.0 ** -24 * np.abs(ref))
+
+
+@pytest.mark.parametrize("cin", [16, 64, 128])
+@pytest.mark.parametrize("fmax,wscale", [(3.4028235e38, 1e-4), (3.0e38, 1e-30), (1e33, 1.0), (1e-37, 1.0), (1e-36, 1e30)])
+def test_ends_of_the_range(cin, fmax, wscale):
+    """Features up to the largest float (which rounds to infinity in bf16) and
+    down to the smallest normal ones: sums that fp32 holds stay finite."""
+    H, W = 37, 41
+    rng = np.random.default_rng(cin)
+    w = (rng.standard_normal((32, cin, 3, 3)) * wscale / (9 * cin)).astype(np.float32)
+    eng = _layer(cin, 32, 1, "f32", w, H, W)
+    idx, f = _window(rng, 500, cin, H, W, 1.0, "f32")
+    f = np.clip(f, -1, 1) * np.float32(fmax)                # many are exactly +-fmax
+    _step(eng, (idx, f), "f32", True)
+    # planes end at 2^-133 and products at 2^-149
+    ref = _conv(_canvas((idx, f), cin, H, W), w, 1)
+    mag = _conv(np.abs(_canvas((idx, f), cin, H, W)), np.abs(w), 1)
+    tiny = 9 * cin * (2.0 ** -133 * np.abs(w).max() + 2.0 ** -133 * fmax * (wscale < 1e-20) + 2.0 ** -149)
+    out = eng.read(1)
+    torch.cuda.synchronize()
+    got = out.cpu().numpy().astype(np.float64)
+    eps = 2.0 ** -24 + 2.0 ** -34 + (3 * 9 * max(1, cin // 32) + 16) * 2.0 ** -24
+    assert np.all(np.abs(got - ref) <= eps * mag + tiny)
+
+
 @pytest.mark.parametrize("cin", [16, 64, 128])
 @pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan])
 def test_values_that_are_not_finite(cin, value):
@@ -135,6 +219,11 @@ def test_values_that_are_not_finite(cin, value):
     under = np.zeros((H, W), bool)
     under[max(r - 1, 0):r + 2, max(c - 1, 0):c + 2] = True
     assert not np.isfinite(got[under]).any()
+    if np.isinf(value):                                     # infinite, with the weight's sign
+        sign = np.sign(value) * np.sign(w[:, cin // 2])
+        for i in range(max(r - 1, 0), min(r + 2, H)):
+            for j in range(max(c - 1, 0), min(c + 2, W)):
+                np.testing.assert_array_equal(got[i, j], np.inf * sign[:, r - i + 1, c - j + 1])
     f[at, cin // 2] = 0.0
     ref = _conv(_canvas((idx, f), cin, H, W), w, 1)
     np.testing.assert_allclose(got[~under], ref[~under], rtol=0, atol=1e-5 * np.abs(ref).max())
@@ -159,3 +248,57 @@ def test_first_pass_of_neck_inputs_of_16_and_32_channels():
     torch.cuda.synchronize()
     # three layers in a chain, each off by at most about 2e-6 of its largest sum
     np.testing.assert_allclose(out.cpu().numpy(), ref, rtol=0, atol=6e-6 * np.abs(ref).max())
+
+
+@pytest.mark.parametrize("cin,cout,s", [(16, 16, 1), (16, 32, 2), (32, 32, 2), (64, 64, 1), (128, 128, 2), (256, 64, 4)])
+def test_upsampler_of_unlike_channels(cin, cout, s):
+    """An upsampler behind a layer that passes its input on: channels 2^60 apart
+    with weights the other way round, then an infinity and a value that rounds
+    to one in bf16."""
+    from paper_2512_08557_amd import Engine
+    H, W = 21, 19
+    rng = np.random.default_rng(cin + s)
+    same = np.zeros((cin, cin, 3, 3), np.float32)
+    same[np.arange(cin), np.arange(cin), 1, 1] = 1.0
+    sc = _unlike(rng, cin, 60)
+    u = (rng.standard_normal((cin, cout, s, s)) / sc[:, None, None, None]).astype(np.float32)
+    eng = Engine(H, W, cin, [(cin, cin, 1, False)], [same], max_pillars=H * W, ups=[(1, cout, s, False)], up_weights=[u])
+    idx, f = _window(rng, 150, cin, H, W, 1.0, "f32")
+    f *= sc
+    _step(eng, (idx, f), "f32", True)
+    out = eng.read(2)
+    torch.cuda.synchronize()
+    got = out.cpu().numpy().astype(np.float64)
+
+    def up(x, w):
+        return np.einsum("hwc,cdab->hawbd", x, w.astype(np.float64)).reshape(H * s, W * s, cout)
+
+    x = _canvas((idx, f), cin, H, W)
+    eps = 2.0 ** -24 + 2.0 ** -34 + (3 * max(1, cin // 32) + 2) * 2.0 ** -24
+    tol = eps * up(np.abs(x), np.abs(u))
+    assert np.all(np.abs(got - up(x, u)) <= tol)
+    # the next window, with special values in two pillars
+    g = f.copy()
+    inf_at, big_at = 40, 90
+    g[inf_at, 3] = np.inf
+    g[big_at, np.argmax(sc)] = 3.4028235e38                 # the channel with the smallest weights
+    _step(eng, (idx, g), "f32", True)
+    out = eng.read(2)
+    torch.cuda.synchronize()
+    got2 = out.cpu().numpy().astype(np.float64)
+    r, c = divmod(int(idx[inf_at]), W)
+    # (the layer's zero weights make NaNs of the infinity in its other channels
+    # and in the cells around it)
+    assert not np.isfinite(got2[r * s:r * s + s, c * s:c * s + s]).any()
+    g[inf_at] = 0.0
+    y = _canvas((idx, g), cin, H, W)
+    want = up(y, u)
+    # a stride adds what changed: the sums of both windows count
+    tol = tol + eps * up(np.abs(x) + np.abs(y), np.abs(u))
+    ok = np.ones((H * s, W * s), bool)
+    ok[max(r - 1, 0) * s:(r + 2) * s, max(c - 1, 0) * s:(c + 2) * s] = False
+    assert np.all((np.abs(got2 - want) <= tol)[ok])
+    same_cells = ok.copy()
+    r, c = divmod(int(idx[big_at]), W)
+    same_cells[r * s:r * s + s, c * s:c * s + s] = False
+    np.testing.assert_array_equal(got2[same_cells], got[same_cells])
