@@ -17,16 +17,16 @@
 //
 // Every change set is the set of cells stamped with the stride's epoch in a
 // per-grid stamp map, and every delta row sits at its cell's position;
-// bumping the epoch invalidates every set at once, so no per-stride clears are
-// needed.  The output sets of the layers are also compacted into lists of
-// NSHARD segments.  The two counter sets alternate between strides; the
-// detect launch clears the set the next stride will use.
+// bumping the epoch invalidates every set at once.  The output sets of the
+// layers are also compacted into lists of NSHARD segments.  The two counter
+// sets, and on handles whose lists are compacted (plan_lists) the two bitmaps
+// of the first layer's list, alternate between strides; the detect launch
+// clears those the next stride will use.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <cmath>
 #include <cstdio>
-#include <cstdlib>
 #include <cstring>
 #include <new>
 #include <vector>
@@ -45,7 +45,7 @@ struct LayerState {
     void* wpack = nullptr;
     uint32_t* stamp = nullptr;
     int32_t* list = nullptr; // NSHARD segments of Hout*Wout cells
-    // layers after the first of a backbone without active sets (plan.h)
+    // layers after the first of a handle whose lists are compacted (plan.h)
     uint32_t* bits = nullptr;   // the change list as a bitmap, wpr(Wout) words a row
     uint16_t* taps = nullptr;   // every list entry's changed taps
     void* delta = nullptr;   // delta rows of this layer's output, dense by cell (nullptr for the last layer)
@@ -96,7 +96,7 @@ struct sscater {
     uint64_t* pres = nullptr;
     uint32_t* stamp0 = nullptr;
     void* delta0 = nullptr;        // input delta rows, dense by cell
-    // the first layer's list as a bitmap by cell index, for the second's plan;
+    // with plan: the first layer's list as a bitmap by cell index, for the second's;
     // alternating between strides: the detection of one clears the other's
     uint32_t* flat[2] = {nullptr, nullptr};
     int flat_n = 0;                // 16-byte values of one
@@ -114,6 +114,7 @@ struct sscater {
     int32_t* err_host = nullptr;   // host-visible sticky error word
     int32_t* err_dev = nullptr;
     bool sparse = false;           // regular sparse + submanifold layers
+    bool plan = false;             // lists after the first by stream compaction (plan_lists)
     // points mode: the incremental pillar feature net in front of the layers
     bool pfn = false;
     sscater_pfn pfn_spec{};
@@ -260,11 +261,15 @@ PropTarget prop_target(sscater* h, int l /* consuming layer, 1..L */, int set) {
     t.list = ls.list;
     t.count = h->cnt_ptr(set, l);
     t.pairs = h->pairs_ptr(set, l);
-    t.bits = l == 1 && !h->sparse ? h->flat[set] : nullptr;
+    t.bits = l == 1 && h->plan ? h->flat[set] : nullptr;
     return t;
 }
 
 int words_of(int n) { return (n + 31) / 32; }
+
+// Whether the lists of the layers after the first come from compactions
+// (plan.h); on sparse handles they come from the tiles' footprint stamps.
+bool plan_lists(int n) { return n > 1; }
 
 // The compaction that builds layer l's list (l >= 2) in the launch of layer
 // l - 1.  A workgroup takes a tile of 128 words (whole rows, or parts of rows
@@ -331,11 +336,16 @@ int run_layers(sscater* h, int set, uint32_t epoch, hipStream_t s) {
         a.epoch = epoch;
         a.dimg = FastDiv((uint32_t)(ls.Hout * ls.Wout));
         a.drow = FastDiv((uint32_t)ls.Wout);
-        a.taps = h->sparse ? nullptr : ls.taps;
-        if (l < h->L && !h->sparse) a.plan = plan_args(h, l + 1, set);
+        a.taps = ls.taps;
+        if (l < h->L) {
+            if (h->plan) {
+                a.plan = plan_args(h, l + 1, set);
+            } else {
+                a.has_next = 1;
+                a.next = prop_target(h, l + 1, set);
+            }
+        }
         if (h->sparse) {
-            a.has_next = l < h->L;
-            if (a.has_next) a.next = prop_target(h, l + 1, set);
             a.memb = ls.memb;
             if (!ls.sub)      // a regular layer passes its membership changes to the next regular layer
                 for (int k = l + 1; k <= h->L; ++k)
@@ -351,7 +361,7 @@ int run_layers(sscater* h, int set, uint32_t epoch, hipStream_t s) {
             a.n_cum = h->nlines();
         }
         e = timed_launch(h, 1 + l, s, [&](const LaunchCtx& c) {
-            return launch_layer(a, ls.spec.cin, ls.spec.cout, ls.spec.stride, h->bf16, h->sparse, c);
+            return launch_layer(a, ls.spec.cin, ls.spec.cout, ls.spec.stride, h->bf16, h->sparse || a.has_next, c);
         });
         if (e != hipSuccess) return hip_fail(e);
     }
@@ -410,7 +420,7 @@ namespace {
 
 int create_impl(const sscater_grid* grid, int32_t batch, const sscater_layer* layers, int32_t n_layers,
                 const void* const* weights, const sscater_upsampler* ups, int32_t n_ups,
-                const void* const* up_weights, sscater_t* out) {
+                const void* const* up_weights, bool sparse, sscater_t* out) {
     // ---- validation: host only, before any HIP call ----
     if (!grid || !layers || !weights || !out) return SSCATER_E_INVALID_ARG;
     if (batch < 1 || (batch > 1 && n_ups > 0)) return SSCATER_E_INVALID_ARG;
@@ -467,6 +477,8 @@ int create_impl(const sscater_grid* grid, int32_t batch, const sscater_layer* la
     h->L = n_layers;
     h->bf16 = bf16;
     h->row_bytes = row_bytes;
+    h->sparse = sparse;
+    h->plan = !sparse && plan_lists(n_layers);
     hipError_t he = hipGetDevice(&h->device);
     if (he != hipSuccess) {
         delete h;
@@ -517,11 +529,11 @@ int create_impl(const sscater_grid* grid, int32_t batch, const sscater_layer* la
             SSC_TRY(dev_alloc(h, (void**)&ls.Z, oc * ls.spec.cout * 4));
             SSC_TRY(dev_alloc(h, (void**)&ls.stamp, oc * 4));
             SSC_TRY(dev_alloc(h, (void**)&ls.list, oc * 4 * NSHARD));
-            if (l == 0 && n_layers > 1) {
+            if (l == 0 && h->plan) {
                 h->flat_n = (int)((oc / 32 + 2 + 3) / 4);   // one word past the last cell's
                 for (int k = 0; k < 2; ++k) SSC_TRY(dev_alloc(h, (void**)&h->flat[k], (size_t)h->flat_n * 16));
             }
-            if (l > 0) {
+            if (l > 0 && h->plan) {
                 SSC_TRY(dev_alloc(h, (void**)&ls.bits, (size_t)batch * ls.Hout * words_of(ls.Wout) * 4));
                 SSC_TRY(dev_alloc(h, (void**)&ls.taps, oc * 2 * NSHARD));
             }
@@ -587,12 +599,12 @@ extern "C" {
 int sscater_create_neck(const sscater_grid* grid, const sscater_layer* layers, int32_t n_layers,
                         const void* const* weights, const sscater_upsampler* ups, int32_t n_ups,
                         const void* const* up_weights, sscater_t* out) {
-    return create_impl(grid, 1, layers, n_layers, weights, ups, n_ups, up_weights, out);
+    return create_impl(grid, 1, layers, n_layers, weights, ups, n_ups, up_weights, false, out);
 }
 
 int sscater_create_batched(const sscater_grid* grid, int32_t batch, const sscater_layer* layers, int32_t n_layers,
                            const void* const* weights, sscater_t* out) {
-    return create_impl(grid, batch, layers, n_layers, weights, nullptr, 0, nullptr, out);
+    return create_impl(grid, batch, layers, n_layers, weights, nullptr, 0, nullptr, false, out);
 }
 
 // sorted: the caller's cell indices increase strictly (sscater_step_sorted)
@@ -632,7 +644,7 @@ static int step_impl(sscater_t h, const sscater_pillars* pl, void* stream, bool 
     d.delta0 = h->delta0;
     d.zero_ptr = h->set_ptr(set ^ 1);
     d.zero_n = h->nlines();
-    d.clear = h->sparse ? nullptr : reinterpret_cast<uint4*>(h->flat[set ^ 1]);
+    d.clear = reinterpret_cast<uint4*>(h->flat[set ^ 1]);
     d.clear_n = h->flat_n;
     d.HW = (int32_t)cells;
     d.epoch = epoch;
@@ -842,7 +854,7 @@ int sscater_create_sparse(const sscater_grid* grid, const sscater_layer* layers,
         if ((submanifold[l] != 0 && submanifold[l] != 1) || (submanifold[l] == 1 && layers[l].stride != 1))
             return SSCATER_E_INVALID_ARG;
     sscater_t h = nullptr;
-    int rc = sscater_create_neck(grid, layers, n_layers, weights, nullptr, 0, nullptr, &h);
+    int rc = create_impl(grid, 1, layers, n_layers, weights, nullptr, 0, nullptr, true, &h);
     if (rc != SSCATER_OK) return rc;
     DeviceGuard dg(h->device);
     if (!dg.ok) {
@@ -859,7 +871,6 @@ int sscater_create_sparse(const sscater_grid* grid, const sscater_layer* layers,
             return rc;
         }
     }
-    h->sparse = true;
     *out = h;
     return SSCATER_OK;
 }

@@ -189,3 +189,25 @@ def test_sorted_large_list_matches_two_pass_bitwise():
             assert torch.equal(e1.read(l).view(torch.int32), e2.read(l).view(torch.int32)), f"{where}: map {l}"
     e1.close()
     e2.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_memory_of_a_handle(dtype):
+    """A sparse handle of 16-channel layers takes, per cell, the canvas, its
+    presence word, stamp and delta row, and per layer the map, stamp, list,
+    active-set word and (but for the last) delta row: no row wider than its
+    channels, nothing that only other handles use."""
+    import torch
+    from paper_2512_08557_amd import Engine
+    H = W = 2048
+    ws = [np.zeros((16, 16, 3, 3), np.float32)] * 3
+    Engine(64, 64, 16, [(16, 16, 1, True)], ws[:1], dtype=dtype, max_pillars=64).close()   # the library's own
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    eng = Engine(H, W, 16, [(16, 16, 1, True)] * 3, ws, dtype=dtype, max_pillars=64, submanifold=[False, True, False])
+    taken = free - torch.cuda.mem_get_info()[0]
+    row = 16 * (2 if dtype == "bf16" else 4)
+    cell = (row + 8 + 4 + 64) + 3 * (64 + 4 + 8) + 2 * 8 + 2 * 64
+    # (large buffers are whole 2 MB pages here; the small ones share chunks of 4 MB)
+    assert taken <= H * W * cell + 16 * 2 ** 20, f"{taken / 2**20:.0f} MiB for {H * W * cell / 2**20:.0f}"
+    eng.close()
