@@ -268,8 +268,24 @@ PropTarget prop_target(sscater* h, int l /* consuming layer, 1..L */, int set) {
 int words_of(int n) { return (n + 31) / 32; }
 
 // Whether the lists of the layers after the first come from compactions
-// (plan.h); on sparse handles they come from the tiles' footprint stamps.
-bool plan_lists(int n) { return n > 1; }
+// (plan.h) or from the tiles' own footprint stamps, as on sparse handles.  A
+// compaction reads its whole grid, so its time grows with the grid, the
+// footprint's with the list.  Measured per stride, compaction against
+// footprint, three fp32 layers of 16 channels, 20 / 400 / 4000 changed pillars:
+// 504x504 and 300 pillars 24 against 27 us; 2048x2048 (2^17 words) 25 / 33 / 97
+// against 22 / 33 / 132; 4096x4096 48 / 48 / 125 against 23 / 34 / 133 (64
+// channels 55 / 79 / 239 against 28 / 58 / 276).  So grids of more than 2^17
+// words take the footprint.
+bool plan_lists(const sscater_grid* grid, int batch, const sscater_layer* layers, int n) {
+    int H = grid->H, W = grid->W;
+    long long words = 0;
+    for (int l = 0; l < n; ++l) {
+        H = out_extent(H, layers[l].stride);
+        W = out_extent(W, layers[l].stride);
+        if (l > 0) words = std::max(words, (long long)batch * H * words_of(W));
+    }
+    return n > 1 && words <= (1 << 17);
+}
 
 // The compaction that builds layer l's list (l >= 2) in the launch of layer
 // l - 1.  A workgroup takes a tile of 128 words (whole rows, or parts of rows
@@ -478,7 +494,7 @@ int create_impl(const sscater_grid* grid, int32_t batch, const sscater_layer* la
     h->bf16 = bf16;
     h->row_bytes = row_bytes;
     h->sparse = sparse;
-    h->plan = !sparse && plan_lists(n_layers);
+    h->plan = !sparse && plan_lists(grid, batch, layers, n_layers);
     hipError_t he = hipGetDevice(&h->device);
     if (he != hipSuccess) {
         delete h;

@@ -35,8 +35,9 @@
 //   * epilogue in registers: Z_new = Z_old + D; store Z_new; write the next
 //     layer's delta row at the cell;
 //   * the next layer's change list (the structural rule, including stride-2
-//     downsampling) is built by the launch's first workgroups (plan.h), or in
-//     sparse backbones, where it depends on the active sets, by the tiles.
+//     downsampling) is built by the launch's first workgroups (plan.h), or by
+//     the tiles: in sparse backbones, where it depends on the active sets, and
+//     on very large grids (the host's plan_lists).
 //
 // MFMA operand layout (v_mfma_f32_16x16x32_bf16):
 //   src0 = weights, lane l supplies row cout = l%16, k = 8*(l/16) .. +7;
@@ -64,7 +65,7 @@
 // shared, a barrier per stage) a 256->256 launch took 8.5 us more, and with
 // the delta rows loaded in operand order straight into registers 4.2.
 //
-// Sparse backbones (SPARSE = true): a site inactive in this and in the
+// Sparse backbones (SPARSE = true, a.memb set): a site inactive in this and in the
 // previous stride neither changes nor propagates; an inactive site's output is
 // zero in the delta epilogue; the first layer of a block passes its sites'
 // membership changes to the next block's active-set counts (SPREAD).  Z is
@@ -270,11 +271,12 @@ __device__ __forceinline__ void layer_tiles(const int32_t* __restrict__ plist, c
                 const int co = min(c0 + i * 16 + 4 * g, COUT - 4);
                 zo[i] = *reinterpret_cast<const f4v*>(a.Z + (size_t)q * COUT + co);
             }
-            if constexpr (SPARSE) {
-                const uint64_t mw = a.memb[q];
-                now = memb_now(mw);
-                prev = memb_prev(mw, a.epoch);
-            }
+            if constexpr (SPARSE)
+                if (a.memb) {                            // uniform
+                    const uint64_t mw = a.memb[q];
+                    now = memb_now(mw);
+                    prev = memb_prev(mw, a.epoch);
+                }
         }
         ch = ch && ev == a.epoch;
         if (tt < 9) rowcell[tt][tr] = ch ? cell : -1;

@@ -1,5 +1,6 @@
 // The next layer's change list by stream compaction (PlanArgs): one workgroup
-// per tile of rows, inside a layer kernel's launch.
+// per tile of rows, inside a layer kernel's launch (all but sparse backbones and
+// very large grids, whose lists come from the tiles).
 //
 // Method (SSCATeR, arXiv 2512.08557, Alg. 1): every output site touched by the
 // scatter of a changed site is changed; with 3x3 kernels that is a dilation of

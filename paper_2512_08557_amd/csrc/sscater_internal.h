@@ -62,7 +62,7 @@ struct FastDiv {
 
 // The next layer's change list as a stream compaction (backbones without
 // active sets, whose change sets follow from the layer before by the
-// structural rule alone): A_l as a bitmap -> A_{l+1} as a bitmap, a list with every entry's changed taps,
+// structural rule alone; not on very large grids): A_l as a bitmap -> A_{l+1} as a bitmap, a list with every entry's changed taps,
 // stamps, and the counters.  Workgroups of layer l's own launch, one per
 // tile of the target grid (whole rows, or parts of very long ones).
 struct PlanArgs {
@@ -152,7 +152,7 @@ struct LayerArgs {
     FastDiv dimg, drow;         // division by Hout * Wout, and by Wout
     const uint16_t* taps;       // every list entry's changed taps (nullptr: by the stamps)
     PlanArgs plan;              // the next layer's list
-    // sparse backbones: the next layer's list, from this launch's tiles
+    // without plans: the next layer's list, from this launch's tiles
     int has_next;
     PropTarget next;
     // sparse backbones: this layer's output active-set words, and where a

@@ -1,7 +1,8 @@
 """Change lists built by stream compaction (every layer after the first): grid
 widths around the 32-cell words, rows of one word and of more than a tile's
 words, single rows and columns, both strides, batches, sparse and full change
-sets.  The lists, pair counts and maps are checked against the oracle."""
+sets; and very large grids, whose lists come from the layers' tiles.  The
+lists, pair counts and maps are checked against the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -84,3 +85,33 @@ def test_grid_shapes(H, W, chain):
 @pytest.mark.parametrize("chain", sorted(CHAINS))
 def test_batches(chain):
     _run(37, 45, CHAINS[chain], 0.05, batch=3)
+
+
+@pytest.mark.parametrize("W,batch", [(2, 4), (2, 5), (33, 3)])
+@pytest.mark.parametrize("chain", ["s1s1", "s1s2s1"])
+def test_grids_on_either_side_of_the_rule(W, batch, chain):
+    """2^17 words of 32 cells (a row has one at least) is the largest grid whose
+    lists are compacted: 4 x 32767 rows of one word are just below, 5 x 32767 and
+    3 x 32767 rows of two above (in the layers before stride 2)."""
+    _run(32767, W, CHAINS[chain], 0.002, batch=batch)
+
+
+def test_a_stride_of_a_large_grid_takes_the_time_of_its_changes():
+    """Twenty changed pillars on 4096x4096: a compaction of the whole grid per
+    layer took 48 us a stride (58 with the bitmap's clear), the tiles' footprint
+    23."""
+    from paper_2512_08557_amd import Engine
+    H = W = 4096
+    rng = np.random.default_rng(0)
+    ws = [(rng.standard_normal((16, 16, 3, 3)) / 12).astype(np.float32)] * 3
+    eng = Engine(H, W, 16, [(16, 16, 1, True)] * 3, ws, max_pillars=64)
+    idx = torch.from_numpy(np.sort(rng.choice(H * W, 20, replace=False)).astype(np.int32)).cuda()
+    f = [torch.from_numpy(rng.standard_normal((20, 16)).astype(np.float32)).cuda() for _ in range(2)]
+    for k in range(6):
+        eng.step(idx, f[k & 1], sorted=True)
+    eng.profile(True)
+    for k in range(20):
+        eng.step(idx, f[k & 1], sorted=True)
+    ms, _cnt = eng.profile_read()
+    eng.profile(False)
+    assert sum(ms) / 20 < 0.040, f"{1e3 * sum(ms) / 20:.1f} us of kernels per stride"
