@@ -291,7 +291,10 @@ bool plan_lists(const sscater_grid* grid, int batch, const sscater_layer* layers
 // l - 1.  A workgroup takes a tile of 128 words (whole rows, or parts of rows
 // longer than 4096 cells), more on grids of over 64 such tiles (up to what its
 // LDS holds): at 432x496 a dozen workgroups that end before the layer's own,
-// and still few on four 1024x1024 images.
+// and still few on four 1024x1024 images.  A small grid is cut into sixteen
+// tiles, of 32 words at least, since one workgroup's chain over all of it
+// outlasts a small layer (two 16-channel layers on 64x64, a stride: 19.1 us
+// with one tile, 17.1 with four; 150x130, three layers: 26.3 -> 23.2).
 PlanArgs plan_args(sscater* h, int l, int set) {
     PlanArgs p{};
     const LayerState& ls = h->layers[l - 1];
@@ -304,7 +307,8 @@ PlanArgs plan_args(sscater* h, int l, int set) {
     p.Wout = ls.Wout;
     p.wpo = words_of(ls.Wout);
     const long long words = (long long)h->batch * p.Hout * p.wpo;
-    const int want = (int)std::min<long long>(PLAN_WORDS, std::max<long long>(128, (words + 63) / 64));
+    const long long small = std::min<long long>(128, std::max<long long>(32, (words + 15) / 16));
+    const int want = (int)std::min<long long>(PLAN_WORDS, std::max(small, (words + 63) / 64));
     p.cols = std::min(p.wpo, want);
     p.chunks = (p.wpo + p.cols - 1) / p.cols;
     p.rows = std::max(1, std::min(p.Hout, want / p.cols));

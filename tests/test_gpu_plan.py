@@ -115,3 +115,22 @@ def test_a_stride_of_a_large_grid_takes_the_time_of_its_changes():
     ms, _cnt = eng.profile_read()
     eng.profile(False)
     assert sum(ms) / 20 < 0.040, f"{1e3 * sum(ms) / 20:.1f} us of kernels per stride"
+
+
+def test_a_small_grid_is_cut_into_several_tiles():
+    """Two 16-channel layers on 64x64 whose launches also build the next list,
+    and one that does not.  One workgroup over the whole grid took 7.0 us beside
+    the last layer's 4.1; four take 4.8."""
+    from paper_2512_08557_amd import Engine
+    rng = np.random.default_rng(0)
+    ws = [(rng.standard_normal((16, 16, 3, 3)) / 12).astype(np.float32)] * 3
+    eng = Engine(64, 64, 16, [(16, 16, 1, True)] * 3, ws, max_pillars=400)
+    idx = torch.from_numpy(np.sort(rng.choice(64 * 64, 400, replace=False)).astype(np.int32)).cuda()
+    f = [torch.from_numpy(rng.standard_normal((400, 16)).astype(np.float32)).cuda() for _ in range(2)]
+    for k in range(10):
+        eng.step(idx, f[k & 1], sorted=True)
+    eng.profile(True)
+    for k in range(50):
+        eng.step(idx, f[k & 1], sorted=True)
+    ms, _cnt = eng.profile_read()
+    assert ms[2] + ms[3] < 2 * 1.4 * ms[4], [f"{m / 50 * 1e3:.2f} us" for m in ms]
