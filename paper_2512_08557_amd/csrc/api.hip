@@ -48,6 +48,8 @@ struct LayerState {
     // layers after the first of a handle whose lists are compacted (plan.h)
     uint32_t* bits = nullptr;   // the change list as a bitmap, wpr(Wout) words a row
     uint16_t* taps = nullptr;   // every list entry's changed taps
+    PlanArgs plan[2];           // what builds its list, per counter set
+    FastDiv dimg, drow;         // division by Hout * Wout, and by Wout
     void* delta = nullptr;   // delta rows of this layer's output, dense by cell (nullptr for the last layer)
     // sparse backbones: the output active-set words (owned by a regular
     // layer, shared with the submanifold layers of its block)
@@ -152,12 +154,12 @@ struct sscater {
     size_t cells_of(int l) const {
         return (size_t)batch * (l == 0 ? (size_t)grid.H * grid.W : (size_t)layers[l - 1].Hout * layers[l - 1].Wout);
     }
-    int32_t* cnt_ptr(int set, int l) { return set_ptr(set) + (size_t)l * NSHARD * CSTRIDE; }
-    int32_t* pairs_ptr(int set, int l) {
+    int32_t* cnt_ptr(int set, int l) const { return set_ptr(set) + (size_t)l * NSHARD * CSTRIDE; }
+    int32_t* pairs_ptr(int set, int l) const {
         return set_ptr(set) + ((size_t)(L + 1) * NSHARD + (size_t)l * NSHARD * PSPREAD) * CSTRIDE;
     }
-    int32_t* a0_ptr(int set) { return set_ptr(set) + (size_t)(L + 1) * NSHARD * (1 + PSPREAD) * CSTRIDE; }
-    int32_t* set_ptr(int s) { return counters + (size_t)s * ncnt(); }
+    int32_t* a0_ptr(int set) const { return set_ptr(set) + (size_t)(L + 1) * NSHARD * (1 + PSPREAD) * CSTRIDE; }
+    int32_t* set_ptr(int s) const { return counters + (size_t)s * ncnt(); }
 };
 
 namespace {
@@ -295,7 +297,7 @@ bool plan_lists(const sscater_grid* grid, int batch, const sscater_layer* layers
 // tiles, of 32 words at least, since one workgroup's chain over all of it
 // outlasts a small layer (two 16-channel layers on 64x64, a stride: 19.1 us
 // with one tile, 17.1 with four; 150x130, three layers: 26.3 -> 23.2).
-PlanArgs plan_args(sscater* h, int l, int set) {
+PlanArgs plan_args(const sscater* h, int l, int set) {
     PlanArgs p{};
     const LayerState& ls = h->layers[l - 1];
     const LayerState& src = h->layers[l - 2];
@@ -354,12 +356,12 @@ int run_layers(sscater* h, int set, uint32_t epoch, hipStream_t s) {
         a.Wout = ls.Wout;
         a.relu = ls.spec.relu;
         a.epoch = epoch;
-        a.dimg = FastDiv((uint32_t)(ls.Hout * ls.Wout));
-        a.drow = FastDiv((uint32_t)ls.Wout);
+        a.dimg = ls.dimg;
+        a.drow = ls.drow;
         a.taps = ls.taps;
         if (l < h->L) {
             if (h->plan) {
-                a.plan = plan_args(h, l + 1, set);
+                a.plan = h->layers[l].plan[set];
             } else {
                 a.has_next = 1;
                 a.next = prop_target(h, l + 1, set);
@@ -545,6 +547,8 @@ int create_impl(const sscater_grid* grid, int32_t batch, const sscater_layer* la
             ls.Win = W;
             ls.Hout = out_extent(H, ls.spec.stride);
             ls.Wout = out_extent(W, ls.spec.stride);
+            ls.dimg = FastDiv((uint32_t)(ls.Hout * ls.Wout));
+            ls.drow = FastDiv((uint32_t)ls.Wout);
             const size_t oc = (size_t)batch * ls.Hout * ls.Wout;
             SSC_TRY(dev_alloc(h, (void**)&ls.Z, oc * ls.spec.cout * 4));
             SSC_TRY(dev_alloc(h, (void**)&ls.stamp, oc * 4));
@@ -556,6 +560,7 @@ int create_impl(const sscater_grid* grid, int32_t batch, const sscater_layer* la
             if (l > 0 && h->plan) {
                 SSC_TRY(dev_alloc(h, (void**)&ls.bits, (size_t)batch * ls.Hout * words_of(ls.Wout) * 4));
                 SSC_TRY(dev_alloc(h, (void**)&ls.taps, oc * 2 * NSHARD));
+                for (int k = 0; k < 2; ++k) ls.plan[k] = plan_args(h, l + 1, k);
             }
             bool feeds_up = false;
             for (int u = 0; u < n_ups; ++u) feeds_up = feeds_up || ups[u].src_layer == l + 1;
