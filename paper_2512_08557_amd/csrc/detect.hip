@@ -54,7 +54,7 @@ __device__ __forceinline__ void emit_rows(const DetectArgs& a, int p, int pc, bo
     // stamp the first layer's footprint while the rows are written; a
     // toggled pillar's active-set targets load in the same round trip
     PropBatch<G> pb;
-    prop_issue<G, false>(a.next, pc, gd, sub, a.epoch, pb);
+    prop_issue<G>(a.next, pc, gd, sub, a.epoch, pb);
     MembBatch mb;
     const int md = vanish ? -1 : 1;
     // (only a wavefront with a toggle loads them: the branch is uniform)

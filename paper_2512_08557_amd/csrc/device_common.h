@@ -30,14 +30,9 @@ struct PropBatch {
 };
 
 // cell: a valid cell of the source grid (used for addressing even when
-// inactive); active: whether the cell really changed.
-// UNCOND = true: every lane issues its atomic unconditionally so that no
-// branch joins on the returned value (a join would make the compiler wait for
-// it right there).  A slot without a target stamps a clamped cell next to
-// `cell` with 0, which never changes a stamp (stamps only grow and epochs
-// start at 1); the addresses stay spread over the grid.  Use it where most
-// lanes are active.  UNCOND = false: inactive lanes issue nothing.
-template <int G, bool UNCOND>
+// inactive); active: whether the cell really changed.  Inactive lanes issue
+// nothing.
+template <int G>
 __device__ __forceinline__ void prop_issue(const PropTarget& t, int cell, bool active, int sub, uint32_t epoch,
                                            PropBatch<G>& pb) {
     const int img = cell / (t.Hin * t.Win), loc = cell - img * (t.Hin * t.Win);
@@ -57,13 +52,9 @@ __device__ __forceinline__ void prop_issue(const PropTarget& t, int cell, bool a
         ok = ok && rn >= 0 && rn < t.Hout && cn >= 0 && cn < t.Wout;
         const int q = obase + min(max(rn, 0), t.Hout - 1) * t.Wout + min(max(cn, 0), t.Wout - 1);
         pb.q[it] = ok ? q : -1;
-        if (UNCOND) {
-            pb.old[it] = atomicMax(&t.stamp[q], ok ? epoch : 0u);
-        } else if (ok) {
-            // pb.old is read only where q >= 0; leaving it unset on the other
-            // path avoids a register copy that would wait for the atomic
-            pb.old[it] = atomicMax(&t.stamp[q], epoch);
-        }
+        // pb.old is read only where q >= 0; leaving it unset on the other path
+        // avoids a register copy that would wait for the atomic
+        if (ok) pb.old[it] = atomicMax(&t.stamp[q], epoch);
     }
 }
 
@@ -210,13 +201,6 @@ __device__ __forceinline__ void memb_finish(const MembTarget& t, int cell, int h
     unsigned long long got[9];
     memb_swap(t, cell, hin, win, mb, delta, epoch, got);
     memb_settle(t, cell, hin, win, mb, delta, epoch, got);
-}
-
-__device__ __forceinline__ void memb_spread(const MembTarget& t, int cell, int hin, int win, int delta,
-                                            uint32_t epoch) {
-    MembBatch mb;
-    memb_issue(t, cell, hin, win, true, mb);
-    memb_finish(t, cell, hin, win, mb, delta, epoch);
 }
 
 // prop_finish in two halves, so that the counter's round trip overlaps other

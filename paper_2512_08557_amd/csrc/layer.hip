@@ -303,7 +303,7 @@ __device__ __forceinline__ void layer_tiles(const int32_t* __restrict__ plist, c
         // followed by another one (SPREAD) loads the next regular layer's
         // words of the sites whose activity flips now, so that only their
         // swaps end the tile
-        if (lead && a.has_next) prop_issue<4, false>(a.next, q, vrow && (now || prev), g, a.epoch, pb);
+        if (lead && a.has_next) prop_issue<4>(a.next, q, vrow && (now || prev), g, a.epoch, pb);
         if (SPREAD && lead) memb_issue(a.mnext, q, a.Hout, a.Wout, g == 0 && vrow && now != prev, mbt);
         PropSlots<4> ps;
 

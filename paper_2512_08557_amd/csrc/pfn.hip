@@ -165,7 +165,7 @@ __global__ __launch_bounds__(256) void pfn_kernel(PfnArgs a) {
         if constexpr (BF16) xo_b = static_cast<const uint16_t*>(a.X)[(size_t)c * a.C0 + ch];
         else xo_f = static_cast<const float*>(a.X)[(size_t)c * a.C0 + ch];
         PropBatch<64> pb;
-        prop_issue<64, false>(a.next, c, true, lane, a.epoch, pb);
+        prop_issue<64>(a.next, c, true, lane, a.epoch, pb);
         int n = (int)(tl - hd);
         if (n > a.N) {
             if (lane == 0) flag_error(a.err, ERR_PILLAR_FULL);
