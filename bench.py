@@ -79,62 +79,22 @@ def upload(strides, dtype):
     return out
 
 
-# Profile slots keep their numbers whatever launches a layer takes.  The next
-# four names describe the recorded traces of builds that ran the wide stride-1
-# layers in two launches (contraction and tap sum) and the others in a narrow
-# and a wide kernel; slot_kernel() names what the library launches now.
-def layer_kernel_name(cin: int, cout: int, stride: int, dtype: str) -> str:
-    """Kernel of a one-launch layer in such a trace: the wide-layer kernel takes
-    more than 8 input chunks of 16 channels with cout >= 32, or more than 4
-    with cout >= 128; every other layer the narrow one."""
-    nch = cin // 16
-    wide = (nch > 8 and cout >= 32) or (nch > 4 and cout >= 128)
-    return f"layer_kernel{'_wide' if wide else ''}<{cin},{cout},{stride},{dtype}>"
-
-
-CONTRACT_SHAPES = {(128, 128), (128, 256), (256, 128), (256, 256)}
-
-
-def layer_split(l: int, wl) -> bool:
-    """Whether layer l (1-based) runs in two launches, the contraction of its
-    changed input rows with all nine taps and the tap sum: the wide stride-1
-    layers after the first."""
-    sp = wl.layers[l - 1]
-    return (l >= 2 and sp.stride == 1 and (sp.cin, sp.cout) in CONTRACT_SHAPES
-            and not int(os.environ.get("SSCATER_FUSED_WIDE", "0") or 0))
-
-
 def kernel_name(slot: int, wl, ups=(), points=False) -> str:
-    """Slots: 0/1 detection, 1 + l layer l (its tap sum when split), then the
-    upsamplers, then L + 1 + n_ups + l the contraction launch of layer l."""
-    L, nu = len(wl.layers), len(ups)
+    """The kernel the library launches for a profile slot: 0/1 detection, 1 + l
+    layer l (one launch each), then the upsamplers."""
+    L = len(wl.layers)
     if slot == 0:
         if points:
             return "pillar_update_kernel"
         return "detect_sorted_kernel" if SORTED else "detect_kernel<present>"
     if slot == 1:
         return f"pfn_kernel<{wl.dtype}>" if points else "detect_kernel<vanished>"
-    if slot >= L + 2 + nu:
-        sp = wl.layers[slot - (L + 1 + nu) - 1]
-        return f"contract_kernel<{sp.cin},{sp.cout},{wl.dtype}>"
     if slot >= L + 2:
         u = ups[slot - L - 2]
         cin = wl.layers[u.src - 1].cout
         return f"upsample_kernel<{cin},{u.cout},{u.stride},{wl.dtype}>"
-    l = slot - 1
-    sp = wl.layers[l - 1]
-    if layer_split(l, wl):
-        return f"tap_sum_kernel<{sp.cout},{wl.dtype}>"
-    return layer_kernel_name(sp.cin, sp.cout, sp.stride, wl.dtype)
-
-
-def slot_kernel(slot: int, wl, ups=(), points=False) -> str:
-    """The kernel the library launches for a profile slot: one per layer."""
-    L = len(wl.layers)
-    if 2 <= slot < L + 2:
-        sp = wl.layers[slot - 2]
-        return f"layer_kernel<{sp.cin},{sp.cout},{sp.stride},{wl.dtype}>"
-    return kernel_name(slot, wl, ups, points)
+    sp = wl.layers[slot - 2]
+    return f"layer_kernel<{sp.cin},{sp.cout},{sp.stride},{wl.dtype}>"
 
 
 def layer_work(wl, l: int, act, pairs, launches: int):
@@ -156,8 +116,7 @@ def block_times(wl, ms, K: int, n_ups: int = 0) -> dict:
     """Per-stride kernel time (us) of change detection, of each backbone block
     (a block starts at every stride-2 layer, as the PointPillars blocks do),
     of all blocks together and of the neck, from the per-slot sums of the
-    profile pass (slot 0/1 detection, 1 + l layer l, then the upsamplers,
-    then the contraction launches of layers that take two)."""
+    profile pass (slot 0/1 detection, 1 + l layer l, then the upsamplers)."""
     L = len(wl.layers)
     out = {"detect": (ms[0] + ms[1]) / K * 1e3}
     b, tot = 0, 0.0
@@ -165,9 +124,8 @@ def block_times(wl, ms, K: int, n_ups: int = 0) -> dict:
         if l == 1 or wl.layers[l - 1].stride == 2:
             b += 1
             out[f"block {b}"] = 0.0
-        t = ms[1 + l] + (ms[L + 1 + n_ups + l] if len(ms) > L + 1 + n_ups + l else 0.0)
-        out[f"block {b}"] += t / K * 1e3
-        tot += t / K * 1e3
+        out[f"block {b}"] += ms[1 + l] / K * 1e3
+        tot += ms[1 + l] / K * 1e3
     out["all blocks"] = tot
     if n_ups:
         out["neck"] = sum(ms[L + 2 + u] for u in range(n_ups)) / K * 1e3
@@ -353,12 +311,8 @@ def short_kernel(name: str) -> str:
         return f"detect_sorted_kernel<{t[0]},{dt(t[1])}{passes}>"
     if fn == "detect_kernel" and len(t) in (3, 4):
         return f"detect_kernel<{t[0]},{dt(t[1])},{'vanished' if t[2] == 'true' else 'present'}>"
-    if fn in ("layer_kernel", "layer_kernel_wide") and len(t) in (4, 5, 6):
+    if fn == "layer_kernel" and len(t) in (4, 5, 6):
         return f"{fn}<{t[0]},{t[1]},{t[2]},{dt(t[3])}>"
-    if fn == "contract_kernel" and len(t) == 3:
-        return f"contract_kernel<{t[0]},{t[1]},{dt(t[2])}>"
-    if fn == "tap_sum_kernel" and len(t) == 3:
-        return f"tap_sum_kernel<{t[0]},{dt(t[1])}>"
     if fn == "pfn_kernel" and len(t) == 1:
         return f"pfn_kernel<{dt(t[0])}>"
     return fn + "<" + ",".join(t) + ">"
@@ -367,11 +321,7 @@ def short_kernel(name: str) -> str:
 def launches_per_stride(kernel: str, wl) -> int:
     if kernel.startswith(("detect_kernel", "detect_sorted_kernel", "pillar_update_kernel", "pfn_kernel")):
         return 1
-    L = len(wl.layers)
-    names = [kernel_name(1 + l, wl) for l in range(1, L + 1)]
-    names += [kernel_name(L + 1 + l, wl) for l in range(1, L + 1) if layer_split(l, wl)]
-    now = [slot_kernel(1 + l, wl) for l in range(1, L + 1)]
-    return sum(1 for n in now if n == kernel) or sum(1 for n in names if n == kernel)
+    return sum(1 for l in range(1, len(wl.layers) + 1) if kernel_name(1 + l, wl) == kernel)
 
 
 def _csv_rows(path):
@@ -658,7 +608,7 @@ def run_streams(wl, ws, K: int, W: int, n: int, cpu_seconds, no_cpu: bool, batch
         for slot in range(L + 2):
             if cnt[slot] == 0:
                 continue
-            k = kernels.setdefault(slot_kernel(slot, wl), {"ms": 0.0, "launches": 0, "flops": 0.0})
+            k = kernels.setdefault(kernel_name(slot, wl), {"ms": 0.0, "launches": 0, "flops": 0.0})
             k["ms"] += ms[slot]
             k["launches"] += cnt[slot]
             if slot >= 2:
@@ -954,7 +904,7 @@ def main() -> int:
         for slot in range(2 * L + 2 + nu):
             if cnt[slot] == 0:
                 continue
-            name = slot_kernel(slot, wl, neck, points=spec is not None)
+            name = kernel_name(slot, wl, neck, points=spec is not None)
             k = kernels.setdefault(name, {"ms": 0.0, "launches": 0, "flops": 0.0, "bytes": 0.0})
             k["ms"] += ms[slot]
             k["launches"] += cnt[slot]
@@ -1024,7 +974,7 @@ def main() -> int:
         fms, fcnt = eng.profile_read()
         eng.profile(False)
         floor = {"stride_us": wall_floor,
-                 "kernels_us": {slot_kernel(sl, wl, neck, points=spec is not None): fms[sl] / fcnt[sl] * 1e3
+                 "kernels_us": {kernel_name(sl, wl, neck, points=spec is not None): fms[sl] / fcnt[sl] * 1e3
                                 for sl in range(len(fcnt)) if fcnt[sl]}}
         log(f"[bench] zero-change stride: {floor['stride_us']:.1f} us; per launch "
             + ", ".join(f"{k} {v:.2f} us" for k, v in floor["kernels_us"].items()))

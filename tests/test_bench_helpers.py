@@ -48,42 +48,41 @@ def test_stack_strides_offsets_every_image():
     assert st.feats.shape == (3, 4) and st.feats[2, 0] == 2.0 and st.idx.dtype == np.int32
 
 
-def test_kernel_names_of_the_two_launch_layers():
-    """c3: the 128- and 256-channel stride-1 layers after the first run as a
-    contraction launch plus a tap sum; every other layer keeps one launch."""
+def test_kernel_names_of_the_layers_and_the_neck():
+    """One launch per layer, then one per upsampler."""
+    from types import SimpleNamespace as NS
     wl = S.workload("c3")
     L = len(wl.layers)
     names = [bench.kernel_name(1 + l, wl) for l in range(1, L + 1)]
     assert names[0] == "layer_kernel<64,64,2,f32>"
     assert names[4] == "layer_kernel<64,128,2,f32>"
-    assert names[5:10] == ["tap_sum_kernel<128,f32>"] * 5
-    assert names[10] == "layer_kernel_wide<128,256,2,f32>"
-    assert names[11:] == ["tap_sum_kernel<256,f32>"] * 5
-    split = [l for l in range(1, L + 1) if bench.layer_split(l, wl)]
-    assert split == list(range(6, 11)) + list(range(12, 17))
-    assert bench.kernel_name(L + 1 + 12, wl) == "contract_kernel<256,256,f32>"
-    assert bench.launches_per_stride("contract_kernel<256,256,f32>", wl) == 5
-    assert bench.launches_per_stride("tap_sum_kernel<128,f32>", wl) == 5
+    assert names[5:10] == ["layer_kernel<128,128,1,f32>"] * 5
+    assert names[11:] == ["layer_kernel<256,256,1,f32>"] * 5
+    assert bench.launches_per_stride("layer_kernel<256,256,1,f32>", wl) == 5
     assert bench.launches_per_stride("layer_kernel<64,64,1,f32>", wl) == 3
-    assert not any(bench.layer_split(l, S.workload("c2")) for l in range(1, 5))
+    assert bench.launches_per_stride("layer_kernel<128,256,2,f32>", wl) == 1
+    ups = [NS(src=4, cout=128, stride=1), NS(src=16, cout=128, stride=4)]
+    assert bench.kernel_name(L + 3, wl, ups) == "upsample_kernel<256,128,4,f32>"
+    assert bench.kernel_name(0, wl, points=True) == "pillar_update_kernel"
+    assert bench.kernel_name(1, wl, points=True) == "pfn_kernel<f32>"
 
 
 def test_block_times_split_at_stride_two_layers():
     wl = S.workload("c3")
     L = len(wl.layers)
     K = 2
-    ms = [0.0] * (2 * L + 2)
+    ms = [0.0] * (2 * L + 4)
     ms[0], ms[1] = 0.010, 0.004                       # detection, ms over K strides
     for l in range(1, L + 1):
-        ms[1 + l] = 0.001 * l                         # layer (or tap sum) l
-        if bench.layer_split(l, wl):
-            ms[L + 1 + l] = 0.002                     # its contraction launch
-    b = bench.block_times(wl, ms, K)
+        ms[1 + l] = 0.001 * l
+    ms[L + 2], ms[L + 3] = 0.020, 0.030               # two upsamplers
+    b = bench.block_times(wl, ms, K, n_ups=2)
     assert b["detect"] == pytest.approx(7.0)
     assert b["block 1"] == pytest.approx(sum(0.001 * l for l in range(1, 5)) / K * 1e3)
-    assert b["block 2"] == pytest.approx((sum(0.001 * l for l in range(5, 11)) + 5 * 0.002) / K * 1e3)
-    assert b["block 3"] == pytest.approx((sum(0.001 * l for l in range(11, 17)) + 5 * 0.002) / K * 1e3)
+    assert b["block 2"] == pytest.approx(sum(0.001 * l for l in range(5, 11)) / K * 1e3)
+    assert b["block 3"] == pytest.approx(sum(0.001 * l for l in range(11, 17)) / K * 1e3)
     assert b["all blocks"] == pytest.approx(b["block 1"] + b["block 2"] + b["block 3"])
+    assert b["neck"] == pytest.approx(25.0)
 
 
 def test_detection_slot_names_follow_the_detection_form(monkeypatch):
@@ -102,7 +101,9 @@ def test_detection_slot_names_follow_the_detection_form(monkeypatch):
     assert bench.short_kernel("void ssc::detect_kernel<128, true, true, false>(ssc::DetectArgs)") == \
         "detect_kernel<128,bf16,vanished>"
     assert bench.launches_per_stride("detect_sorted_kernel<256,f32>", wl) == 1
-    assert bench.short_kernel("void ssc::layer_kernel<64, 64, 2, false, true, true>(int const*, int const*, int, "
-                              "ssc::LayerArgs)") == "layer_kernel<64,64,2,f32>"
-    assert bench.short_kernel("void ssc::layer_kernel_wide<128, 256, 2, true, false>(int const*, int const*, int, "
-                              "ssc::LayerArgs)") == "layer_kernel_wide<128,256,2,bf16>"
+    assert bench.short_kernel("void ssc::layer_kernel<64, 64, 2, false, true, true>(int const*, int const*, "
+                              "unsigned short const*, char const*, int, int, ssc::LayerArgs)") == \
+        "layer_kernel<64,64,2,f32>"
+    assert bench.short_kernel("void ssc::layer_kernel<128, 256, 2, true, false, false>(int const*, int const*, "
+                              "unsigned short const*, char const*, int, int, ssc::LayerArgs)") == \
+        "layer_kernel<128,256,2,bf16>"
