@@ -84,21 +84,66 @@ def test_layer_shapes(cin, cout, stride, dtype):
     _check(eng, wins, w, cin, stride, dtype, H, W, f"{cin}->{cout} s{stride} {dtype}")
 
 
-@pytest.mark.parametrize("cells", [0, 1, 15, 16, 17, 31, 32, 33, 63, 64, 65, 511])
-def test_list_lengths_around_tiles(cells):
-    """A stride-2 layer whose input cells are isolated and even: one output
-    cell each, so the change list holds exactly `cells` entries."""
-    H, W, c = 64, 64, 64
-    rng = np.random.default_rng(cells)
-    w = (rng.standard_normal((64, c, 3, 3)) * 0.06).astype(np.float32)
-    eng = _layer(c, 64, 2, "f32", w, H, W)
-    pos = rng.choice(32 * 32, cells, replace=False)
-    idx = np.sort((pos // 32) * 2 * W + (pos % 32) * 2).astype(np.int32)
-    win = (idx, rng.standard_normal((cells, c)).astype(np.float32))
-    note(f"[gpu-test] list of {cells}")
-    _step(eng, win, "f32", True)
-    assert len(eng.changed(1)) == cells
-    _check(eng, [win], w, c, 2, "f32", H, W, f"{cells} cells")
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("c", [32, 64, 128, 256])
+@pytest.mark.parametrize("k", [0, 1, 15, 16, 17, 31, 32, 33, 63, 64, 65, 2047, 2048, 2049, 2063, 2064, 2065, 2079, 2080])
+def test_segment_lengths_around_tiles(k, c, dtype):
+    """A list's two segments of exactly k entries each: pillars that change one
+    cell of either layer each (stride 2, even positions), in pairs side by side,
+    so that every tile of the compaction, which gives either segment half of its
+    cells, holds an even number.  Up to 64 channels, and in fp32 always, lists of
+    up to 2048 entries a segment (16 for each of 128 workgroups) take 16-cell
+    tiles, longer ones 32; wider bf16 layers take 32-cell tiles throughout."""
+    from paper_2512_08557_amd import Engine
+    G = 32 if k < 512 else 96                               # the second layer's grid, G x G
+    H = W = 4 * G
+    rng = np.random.default_rng(c + k)
+    ws = [(rng.standard_normal((co, ci, 3, 3)) * (2.0 / (9 * ci)) ** 0.5).astype(np.float32)
+          for ci, co in ((16, c), (c, 32))]
+    if dtype == "bf16":
+        ws = [_bf16(w) for w in ws]
+    layers = [(16, c, 2, True), (c, 32, 2, False)]
+    eng = Engine(H, W, 16, layers, ws, dtype=dtype, max_pillars=H * W)
+    pair = rng.choice(G * G // 2, k, replace=False)
+    pos = np.concatenate([2 * pair, 2 * pair + 1])          # cells of the second layer's grid
+    idx = np.sort(pos // G * 4 * W + pos % G * 4).astype(np.int32)
+    f = rng.standard_normal((2 * k, 16)).astype(np.float32)
+    if dtype == "bf16":
+        f = _bf16(f)
+    note(f"[gpu-test] segments of {k}, {c} channels {dtype}")
+    _step(eng, (idx, f), dtype, True)
+    assert len(eng.changed(1)) == len(eng.changed(2)) == 2 * k
+    ys = oracle.forward(_canvas((idx, f), 16, H, W), ws, layers, bf16_storage=dtype == "bf16")
+    out = eng.read(2)
+    torch.cuda.synchronize()
+    got, ref = out.float().cpu().numpy().astype(np.float64), ys[1]
+    # two layers of one tap each; bf16 rounds the first one's outputs and its own
+    tol = 1e-6 if dtype == "f32" else 2.0 ** -7
+    assert np.abs(got - ref).max(initial=0) <= tol * max(np.abs(ref).max(initial=0), 1e-30)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("cin,cout", [(64, 64), (128, 8), (128, 128), (256, 256)])
+def test_lists_on_either_side_of_the_tile_height(cin, cout, dtype):
+    """Lists somewhat shorter and longer than what 16-cell tiles take, for one to
+    four groups of 64 output channels (256 workgroups walk two segments of each)."""
+    H, W = 200, 200
+    rng = np.random.default_rng(cin + cout)
+    w = (rng.standard_normal((cout, cin, 3, 3)) * (2.0 / (9 * cin)) ** 0.5).astype(np.float32)
+    if dtype == "bf16":
+        w = _bf16(w)
+    most = 2 * 16 * (256 // (2 * max(1, cout // 64)))
+    eng = _layer(cin, cout, 1, dtype, w, H, W)
+    wins = []
+    for rows in (most * 3 // 4 // W, most * 5 // 4 // W + 1):   # of changed cells, and one more in the list
+        f = rng.standard_normal((rows * W, cin)).astype(np.float32)
+        wins.append((np.arange(rows * W, dtype=np.int32), _bf16(f) if dtype == "bf16" else f))
+    for win, longer in zip(wins, (False, True)):
+        _step(eng, win, dtype, True)
+        n = len(eng.changed(1))
+        # (the two segments of a detected list differ by a workgroup's cells or so)
+        assert n > most * 1.1 if longer else n < most * 0.95
+    _check(eng, wins, w, cin, 1, dtype, H, W, f"{cin}->{cout} {dtype}")
 
 
 @pytest.mark.parametrize("cin", [16, 64, 256])
