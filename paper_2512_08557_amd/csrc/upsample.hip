@@ -35,8 +35,9 @@ struct UpShape {
     static constexpr int NCH = !BF16 && CIN < 32 ? 1 : 2 * NU;
     static constexpr int NCBT = COUT / 16;
     static constexpr int NOB = S * S * NCBT;              // output blocks per input cell
-    // output blocks per wavefront (the three planes of two blocks of 256
-    // channels are 192 registers, one workgroup per compute unit)
+    // output blocks per wavefront; one of 256 fp32 channels (the three planes
+    // of two blocks are 192 registers and leave one workgroup per compute unit:
+    // the x4 upsampler of the 432x496 backbone took 23.6 us instead of 19.8)
     static constexpr int BPW = NOB >= 8 && (BF16 || NU < 8) ? 2 : 1;
     static constexpr int OBG = (NOB + 4 * BPW - 1) / (4 * BPW);   // workgroups per tile
 };
