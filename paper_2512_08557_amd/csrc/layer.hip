@@ -302,9 +302,11 @@ __device__ __forceinline__ void layer_tiles(const int32_t* __restrict__ plist, c
         // counter's round trip overlaps the contraction); a regular layer
         // followed by another one (SPREAD) loads the next regular layer's
         // words of the sites whose activity flips now, so that only their
-        // swaps end the tile
+        // swaps end the tile (bf16; in fp32 the 18 registers would spill over
+        // the contraction, so they are loaded behind it: the sparse backbone's
+        // stride is the same either way, 234 us)
         if (lead && a.has_next) prop_issue<4>(a.next, q, vrow && (now || prev), g, a.epoch, pb);
-        if (SPREAD && lead) memb_issue(a.mnext, q, a.Hout, a.Wout, g == 0 && vrow && now != prev, mbt);
+        if (BF16 && SPREAD && lead) memb_issue(a.mnext, q, a.Hout, a.Wout, g == 0 && vrow && now != prev, mbt);
         PropSlots<4> ps;
 
         f4v acc[MH][NB];
@@ -413,6 +415,12 @@ __device__ __forceinline__ void layer_tiles(const int32_t* __restrict__ plist, c
                         }
                     }
                 }
+                // (the resident weights are fetched again rather than kept across
+                // this: fewer registers in the kernels that run short of them)
+                if constexpr (L::STAT) {
+#pragma unroll
+                    for (int i = 0; i < DW; ++i) load_w(unit(wt, i), bw[i]);
+                }
             }
         }
 
@@ -441,6 +449,7 @@ __device__ __forceinline__ void layer_tiles(const int32_t* __restrict__ plist, c
             }
             if (vrow && (COUT % 16 == 0 || 4 * g < COUT)) epilogue_unit<COUT, BF16, OB>(a, q, c0, g, zo, d, now, prev);
         }
+        if (!BF16 && SPREAD && lead) memb_issue(a.mnext, q, a.Hout, a.Wout, g == 0 && vrow && now != prev, mbt);
         if (SPREAD && lead) memb_finish(a.mnext, q, a.Hout, a.Wout, mbt, now ? 1 : -1, a.epoch);
         if (lead && a.has_next) prop_write<4>(a.next, shard, pb, ps);
         // the next tile's table may be written now (its barrier orders the

@@ -56,3 +56,22 @@ def test_weights_are_loaded_ahead_of_a_conditional_unit(tmp_path):
             if has["ds_read_b128"] and has["v_mfma"] and has["global_load_dwordx4"]:
                 assert has["global_load_lds"], f"{name}: weights loaded where they are used"
     assert n == 24
+
+
+@pytest.mark.skipif(not os.path.exists(B.HIPCC), reason="needs the HIP compiler")
+def test_the_kernels_fit_their_registers(tmp_path):
+    """Eight wavefronts of a workgroup share a compute unit's registers, 256 each;
+    what does not fit goes to scratch memory in every tile.  fp32 kernels of
+    sparse backbones hold the most (lists, active-set words, three planes): at
+    most 8 registers spill, and no other kernel's."""
+    text = _assembly(tmp_path, [(32, 64, 1), (64, 64, 1), (64, 128, 2), (128, 128, 1), (256, 256, 1)])
+    n = 0
+    for blk in re.split(r"\n  - \.agpr_count", text)[1:]:
+        name = re.search(r"\.name:\s+(\S+)", blk).group(1)
+        m = re.search(r"layer_kernelILi(\d+)ELi(\d+)ELi(\d)ELb(\d)ELb(\d)ELb(\d)", name)
+        if not m:
+            continue
+        n += 1
+        spill = int(re.search(r"\.vgpr_spill_count:\s+(\d+)", blk).group(1))
+        assert spill <= (8 if m.group(4) == "0" and m.group(6) == "1" else 0), f"{name}: {spill} registers"
+    assert n == 30
