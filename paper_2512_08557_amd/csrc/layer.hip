@@ -77,6 +77,8 @@
 
 namespace ssc {
 
+typedef __attribute__((address_space(3))) f4v lds_f4v;
+
 template <int CIN, int COUT, bool BF16, bool SPARSE, int TM = 32>
 struct LayerShape {
     static constexpr int U = units_of(CIN);              // units of a delta row
@@ -108,16 +110,20 @@ struct LayerShape {
     static constexpr bool WLDS = STAT && !BF16 && U == 2;
     static constexpr int RP = WLDS ? 2 : PL;             // weight planes in registers
     static constexpr int WL_LDS = WLDS ? NU * NB * 1024 : 16;
-    // vector loads certainly issued after the copies of unit i and before it
-    // is awaited: first the copies of units 0 .. D - 1 (the weights of units 0
-    // .. DW - 1 come before them), then, behind each unit x, the copies of unit
-    // x + D and the streamed weights of unit x + DW.  Weights of a unit that
-    // only some wavefronts compute are not counted, the compiler may place them
-    // on either side of the wait.  A smaller count waits for more.
+    // vector loads certainly issued after the copies of unit i, and after its
+    // streamed weights, and before it is awaited: first the copies of units 0 ..
+    // D - 1 (the weights of units 0 .. DW - 1 come before them), then, behind
+    // each unit x, the copies of unit x + D and the streamed weights of unit
+    // x + DW.  Weights of a unit that only some wavefronts compute are not
+    // counted, the compiler may place them on either side of the wait.  A
+    // smaller count waits for more.  The unit's weights are waited for with its
+    // copies because the compiler's own wait for them, while copies are in
+    // flight too, is for everything.
     static constexpr int younger(int i) {
+        const bool own = !STAT && i >= DW;
         int n = 0;
-        for (int j = i + 1; j < D; ++j) n += CPU;
-        for (int x = i < D ? 0 : i - D; x < i; ++x) {
+        for (int j = i + 1; j < D && !own; ++j) n += CPU;
+        for (int x = own ? i - DW + 1 : (i < D ? 0 : i - D); x < i; ++x) {
             if (x + D > i && x + D < CNT) n += CPU;
             if (!STAT && x + DW < FULL) n += PL * NB;
         }
@@ -140,11 +146,8 @@ struct LayerShape {
 template <int CIN, int COUT, int S, bool BF16, bool SPARSE, bool SPREAD, int TM>
 __device__ __forceinline__ void layer_tiles(const int32_t* __restrict__ plist, const uint16_t* __restrict__ ptaps,
                                             const char* __restrict__ pweights, int pcap, int n0, int n1, int b, int nwg,
-                                            const LayerArgs& a, int (&rowcell)[9][32],
-                                            char (&as0)[LayerShape<CIN, COUT, BF16, SPARSE>::AS],
-                                            char (&as1)[LayerShape<CIN, COUT, BF16, SPARSE>::AS],
-                                            char (&as2)[LayerShape<CIN, COUT, BF16, SPARSE>::AS2],
-                                            char (&wl)[LayerShape<CIN, COUT, BF16, SPARSE>::WL_LDS]) {
+                                            const LayerArgs& a, int (&rowcell)[9][32], lds_char* as0, lds_char* as1,
+                                            lds_char* as2, lds_char* wl) {
     // rowcell: changed input cell, or -1.  as0, as1, as2: the wavefronts' delta
     // units in flight (one LDS array per slot: the compiler then tracks the
     // copies into each slot separately); at the end slots 0 and 1 take the
@@ -197,7 +200,7 @@ __device__ __forceinline__ void layer_tiles(const int32_t* __restrict__ plist, c
     // (single values: the compiler's copy tracking follows only a short
     // address chain from the slot's array)
     asm("" : "+v"(a_hi), "+v"(a_lo));
-    auto slot = [&](int k) -> lds_char* { return (lds_char*)(k == 0 ? as0 : (k == 1 ? as1 : as2)); };
+    auto slot = [&](int k) -> lds_char* { return k == 0 ? as0 : (k == 1 ? as1 : as2); };
     const char* dbase = static_cast<const char*>(a.delta_in);
     const char* zrow = static_cast<const char*>(a.zero);
     const char* wbase = pweights + (size_t)nb * L::NU * L::WU;   // uniform
@@ -222,7 +225,7 @@ __device__ __forceinline__ void layer_tiles(const int32_t* __restrict__ plist, c
 #pragma unroll
                     for (int k = 0; k < NB; ++k)
                         copy16(wbase + (size_t)unit(w, i) * L::WU + (2 * NB + k) * 1024 + wl16,
-                               (lds_char*)wl + (unit(w, i) * NB + k) * 1024);
+                               wl + (unit(w, i) * NB + k) * 1024);
         }
     }
 
@@ -347,7 +350,7 @@ __device__ __forceinline__ void layer_tiles(const int32_t* __restrict__ plist, c
                     uint4 w3[NB];
 #pragma unroll
                     for (int k = 0; k < NB; ++k) {
-                        if constexpr (L::WLDS) w3[k] = lds16((lds_char*)wl + (unit(wt, i) * NB + k) * 1024 + wl16);
+                        if constexpr (L::WLDS) w3[k] = lds16(wl + (unit(wt, i) * NB + k) * 1024 + wl16);
                         else w3[k] = bv[2 * NB + k];
                     }
                     mfma_unit<CIN, NB, false>(acc[m], bv, bv + NB, w3,
@@ -426,7 +429,7 @@ __device__ __forceinline__ void layer_tiles(const int32_t* __restrict__ plist, c
 
         // partial sums, added in wavefront order by the finishing wavefronts
         auto red = [&](int ww, int j) __attribute__((always_inline)) {   // block j of wavefront ww
-            return reinterpret_cast<f4v*>((j / SB == 0 ? as0 : as1) + ww * SLOT + (j % SB) * 1024) + lane;
+            return reinterpret_cast<lds_f4v*>((j / SB == 0 ? as0 : as1) + ww * SLOT + (j % SB) * 1024) + lane;
         };
         static_assert(MH * NB <= 2 * SB, "partial sums");
 #pragma unroll
@@ -502,12 +505,13 @@ __global__ __launch_bounds__((64 * LayerShape<CIN, COUT, BF16, SPARSE>::NW)) voi
     if constexpr (L::U <= 2 || !BF16) {
         if (max(n0, n1) <= 16 * (nwg / (2 * L::NBN))) {
             layer_tiles<CIN, COUT, S, BF16, SPARSE, SPREAD, 16>(plist, ptaps, pweights, pcap, n0, n1, b, nwg, a, rowcell,
-                                                                as0, as1, as2, wl);
+                                                                (lds_char*)as0, (lds_char*)as1, (lds_char*)as2,
+                                                                (lds_char*)wl);
             return;
         }
     }
-    layer_tiles<CIN, COUT, S, BF16, SPARSE, SPREAD, 32>(plist, ptaps, pweights, pcap, n0, n1, b, nwg, a, rowcell, as0,
-                                                        as1, as2, wl);
+    layer_tiles<CIN, COUT, S, BF16, SPARSE, SPREAD, 32>(plist, ptaps, pweights, pcap, n0, n1, b, nwg, a, rowcell,
+                                                        (lds_char*)as0, (lds_char*)as1, (lds_char*)as2, (lds_char*)wl);
 }
 
 // ---------------------------------------------------------------------------

@@ -75,3 +75,31 @@ def test_the_kernels_fit_their_registers(tmp_path):
         spill = int(re.search(r"\.vgpr_spill_count:\s+(\d+)", blk).group(1))
         assert spill <= (8 if m.group(4) == "0" and m.group(6) == "1" else 0), f"{name}: {spill} registers"
     assert n == 30
+
+
+@pytest.mark.skipif(not os.path.exists(B.HIPCC), reason="needs the HIP compiler")
+def test_the_copy_pipeline_is_not_drained(tmp_path):
+    """256 input channels on dense handles: nine units a wavefront, the copies of
+    three in flight.  Between the first matrix instruction of a tile and its last copy no wait is
+    for everything; the compiler adds such waits where the source waits for less
+    than a unit's weights need."""
+    n = 0
+    for name, body in _kernels(_assembly(tmp_path, [(256, 256, 1), (256, 64, 2)])):
+        if not re.search(r"ELb[01]ELb0ELb0E", name):     # sparse kernels wait for their counters
+            continue
+        lines = [x.strip() for x in body.splitlines()]
+        copies = [k for k, x in enumerate(lines) if x.startswith("global_load_lds")]
+        # tiles: runs of copies; the plan and the epilogues have none
+        units = 0
+        k = copies[0]
+        while k <= copies[-1]:
+            if lines[k].startswith("s_barrier"):
+                units = 0
+            units += lines[k].startswith("v_mfma")
+            if units and any(c > k for c in copies) and re.match(r"s_waitcnt.*vmcnt\(0\)", lines[k]):
+                nxt = next(c for c in copies if c > k)
+                between = any(x.startswith("s_barrier") for x in lines[k:nxt])
+                assert between, f"{name}: line {k} waits for every load in flight"
+            k += 1
+        n += 1
+    assert n == 4
